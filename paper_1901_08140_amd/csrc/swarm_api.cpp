@@ -402,15 +402,66 @@ swarm_launch_opts resolve_opts(const swarm_launch_opts* o, int precision) {
   // 256-instance batch and serving: small items balance uneven work; the slower FP64 lanes
   // lose more to the wait for the slowest lane at every item boundary)
   r.chunk = (o && o->chunk) ? o->chunk : r.block_size * (precision == SWARM_FP64 ? 8 : 4);
-  r.pending_trigger = (o && o->pending_trigger) ? o->pending_trigger : 32;
   r.use_graph = o ? o->use_graph : 0;
   r.block_size = std::max(64, std::min(1024, (r.block_size / 64) * 64));
   r.chunk = std::max(r.block_size, (r.chunk / r.block_size) * r.block_size);
-  r.pending_trigger = std::max(1, std::min(64, r.pending_trigger));
+  r.pending_trigger = (o && o->pending_trigger) ? std::max(1, std::min(64, o->pending_trigger)) : 32;
   r.service_waves = o ? std::max(0, std::min(r.block_size / 64 - 1, o->service_waves)) : 0;
   r.table_layout = (o && o->table_layout == 1) ? 1 : 0;
   r.park_lanes = (o && o->park_lanes) ? std::max(-1, std::min(64, o->park_lanes)) : kParkLanes;
   return r;
+}
+
+bool free_shape(const swarm_launch_opts* o) {
+  return !o || (o->block_size == 0 && o->chunk == 0 && o->pending_trigger == 0 && o->service_waves == 0);
+}
+
+// A team of g lanes tests 2 g trials of its electron at once, so with 2 g above the t trials
+// of a collision it makes about one step per collision; but it holds g lanes for it, so it
+// pays only while the electrons leave lanes of the device idle.  Measured against the one-lane
+// kernel at its best block and trigger (kernel ms, 800-1500 collisions; one lane | teams):
+//   electrons                     25         1000         1e4         2e4        4e4        1e5
+//   93:7 Ar:CO2 2.4 Td FP64   15.8|3.4(16) 19.5|3.5(16) 20.6|7.4(16) 22.2|10.2(8) 21.6|14.7(8) 29.3|30.2(2)
+//   Ar:CO2 8 Td 0.5 T FP32     4.4|1.7(16)  5.7|1.7(16)  5.6|2.6(8)   6.0|3.1(8)   6.1|4.2(8)   7.1|7.7(2)
+//   Ar:CO2 31 Td moving, FP32  3.4|2.0(8)   4.1|2.1(16)  4.1|2.7(8)   4.1|3.3(4)   4.3|4.1(4)   5.1|7.0(2)
+//   argon 10 Td variable FP32  2.7|2.2(4)   3.8|2.4(8)   4.1|2.8(4)   4.4|3.1(4)   4.6|3.8(4)   5.3|5.8(2)
+//   argon 100 Td FP64          3.2|2.1(8)   3.4|2.1(8)   3.4|2.3(4)   3.5|2.9(2)   3.6|4.1(2)   5.4|6.4(2)
+//   argon 100 Td FP32          2.4|1.9(8)   2.7|1.9(8)   2.6|2.1(4)   2.8|2.4(4)   3.0|3.1(4)   3.9|4.7(2)
+//   argon 900 Td FP32          1.9|1.8(4)   2.0|1.8(4)   2.0|2.0(4)   2.2|2.2(2)   2.4|2.6(2)   3.2|4.0(2)
+//   Maxwell gas FP32           1.1|1.4(2)   1.1|1.4(2)   1.2|1.5(2)                1.6|1.9(2)   2.3|2.7(2)
+// The lanes that may be given out are read off these runs: they grow with t, and a team with
+// most of its trials beyond the hit (2 g > 4.5 t) gets fewer.  Few electrons whose collisions
+// take many steps are spread over all SIMDs, fewer teams in a wave, so that a team waits less
+// for the others (argon 1 Td, 1000 electrons: 2.6 against 3.3 ms); otherwise full waves are as
+// fast.
+TeamShape team_shape(double wide, double trials) {
+  TeamShape s;
+  if (!(trials >= 1.2)) return s;
+  const double simds = 4.0 * device_info().n_cu;
+  const double lanes = simds * std::min(300.0, std::max(40.0, 5.0 * trials * trials));
+  int g = 1;
+  while (g < 16 && g < 2.25 * trials) g *= 2;
+  while (g > 1 && wide * g > (2.0 * g > 4.5 * trials ? 0.6 : 1.0) * lanes) g /= 2;
+  if (g == 1) return s;
+  s.lanes = g;
+  const int full = 64 / g;
+  s.per_wave = trials < 6.0 ? full
+                            : static_cast<int>(std::min<double>(full, std::max(1.0, std::ceil(wide / simds))));
+  s.block = wide <= simds * s.per_wave ? 64 : 256;
+  return s;
+}
+
+// Several instances: the electrons that run at once on average, the launch's work over that
+// of its longest electron.
+TeamShape team_shape(const std::vector<int64_t>& n_e, const std::vector<int64_t>& work, const std::vector<double>& trials) {
+  double total = 0.0, longest = 0.0, t = 0.0;
+  for (size_t i = 0; i < n_e.size(); ++i) {
+    const double w = static_cast<double>(work[i]) * trials[i];
+    total += static_cast<double>(n_e[i]) * w;
+    t += static_cast<double>(n_e[i]) * w * trials[i];
+    longest = std::max(longest, w);
+  }
+  return total > 0.0 ? team_shape(total / longest, t / total) : TeamShape{};
 }
 
 }  // namespace swarm_impl
@@ -467,6 +518,7 @@ static swarm_status build_swarm(swarm* h, const swarm_component* comps, int32_t 
   d.trial_bins = params->trial_bins > 0 ? params->trial_bins : 10;
   std::vector<int32_t> entry_bin, bin_first;
   if (params->trial_strategy == SWARM_TRIAL_BINNED) decade_bins(P, emin, G, d.trial_bins, entry_bin, bin_first);
+  d.balance_node = static_cast<uint32_t>(G - 1);
   d.n_bins = entry_bin.empty() ? 0 : static_cast<int32_t>(bin_first.size()) - 1;
   h->has_b = params->B_T > 0.0;
   // one arena for the raw inputs and the tables
@@ -682,6 +734,7 @@ swarm_status swarm_set_launch_opts(swarm_t h, const swarm_launch_opts* opts) {
   if (!h) return fail(SWARM_ERR_INVALID_ARG, "NULL handle");
   if (h->in_flight) return busy();
   h->opts = resolve_opts(opts, h->desc.precision);
+  h->free_shape = free_shape(opts);
   return SWARM_OK;
 }
 
@@ -751,6 +804,12 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
   DeviceInfo& dev = device_info();
   const int ext = d.thermal_targets || d.relativistic ? 2 : d.trial_strategy != SWARM_TRIAL_CONSTANT ? 1 : 0;
   const int per_cu = swarm_kernel_max_blocks_per_cu(d.precision, h->has_b, trace, real, ext, svc, o.block_size, lds);
+  const bool may_team = h->free_shape && !trace;
+  auto team_grid = [&](const TeamShape& t, int64_t groups) {
+    const int64_t resident = static_cast<int64_t>(dev.n_cu) *
+                             swarm_kernel_max_blocks_per_cu(d.precision, h->has_b, false, real, ext, 0, t.block, lds, true);
+    return static_cast<int>(std::max<int64_t>(1, std::min(groups, resident)));
+  };
   if ((e = hipEventRecord(h->ev[0], s)) != hipSuccess) return hip_fail(e, "event");
   if (!real) {
     // enough work items to give every resident work-group several of them
@@ -758,18 +817,23 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     int64_t chunk = (n_electrons + 4 * slots - 1) / (4 * slots);
     chunk = ((chunk + o.block_size - 1) / o.block_size) * o.block_size;
     chunk = std::max<int64_t>(o.block_size, std::min<int64_t>(chunk, o.chunk));
-    std::vector<WorkItem> items;
-    make_items({n_electrons}, {n_collisions}, chunk, items, 0, 0);
+    const TeamShape team = may_team ? team_shape(static_cast<double>(n_electrons), d.trials) : TeamShape{};
+    std::vector<WorkItem> items;   // a team launch takes its ranges from their number alone
+    if (team.lanes == 1) make_items({n_electrons}, {n_collisions}, chunk, items, 0, 0);
+    const int64_t n_items = team.lanes > 1 ? (n_electrons + team.per_group() - 1) / team.per_group()
+                                           : static_cast<int64_t>(items.size());
     if ((e = h->items.ensure(items.size() * sizeof(WorkItem) + 256)) != hipSuccess) return hip_fail(e, "work items");
     h->h_items = items;
     int32_t* d_ctr = reinterpret_cast<int32_t*>(static_cast<char*>(h->items.p) + items.size() * sizeof(WorkItem));
-    if ((e = hipMemcpyAsync(h->items.p, h->h_items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s)) != hipSuccess)
+    if (!items.empty() &&
+        (e = hipMemcpyAsync(h->items.p, h->h_items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s)) != hipSuccess)
       return hip_fail(e, "work items");
     if ((e = launch_fill_u32(reinterpret_cast<uint32_t*>(d_ctr), 0u, 1, s)) != hipSuccess) return hip_fail(e, "item counter");
-    const int grid = std::max(1, std::min<int>(static_cast<int>(items.size()), dev.n_cu * per_cu));
-    if ((e = launch_swarm_dummy(h->d_desc, static_cast<const WorkItem*>(h->items.p), static_cast<int32_t>(items.size()),
-                                d_ctr, d.precision, h->has_b, trace, ext, svc, o.block_size, grid, o.pending_trigger, lds, ch_off,
-                                ll.pool_off, ll.cum_off, s)) != hipSuccess)
+    const int grid = team.lanes > 1 ? team_grid(team, n_items)
+                                    : std::max(1, std::min<int>(static_cast<int>(n_items), dev.n_cu * per_cu));
+    if ((e = launch_swarm_dummy(h->d_desc, items.empty() ? nullptr : static_cast<const WorkItem*>(h->items.p),
+                                static_cast<int32_t>(n_items), d_ctr, d.precision, h->has_b, trace, ext, svc, o.block_size, grid,
+                                o.pending_trigger, lds, ch_off, ll.pool_off, ll.cum_off, s, team)) != hipSuccess)
       return hip_fail(e, "swarm kernel launch");
     h->n_launches = 1;
     h->n_parked = 0;
@@ -800,11 +864,14 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
       if ((e = launch_fill_u64(&d.ctr->gen_next, 0ull, 1, s)) != hipSuccess) return hip_fail(e, "generation counter");
       if ((e = launch_fill_u64(&d.ctr->parked, 0ull, 1, s)) != hipSuccess) return hip_fail(e, "park counter");
       const int64_t want = (n_parked + count + o.block_size - 1) / o.block_size;
-      const int grid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want * 4, static_cast<int64_t>(dev.n_cu) * per_cu)));
+      const TeamShape team = may_team ? team_shape(static_cast<double>(n_parked + count), d.trials) : TeamShape{};
+      const int grid = team.lanes > 1
+          ? team_grid(team, (n_parked + count + team.per_group() - 1) / team.per_group())
+          : static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want * 4, static_cast<int64_t>(dev.n_cu) * per_cu)));
       const int64_t park_min = hc.dropped != 0 || park_lanes == 0 ? 0 : std::max<int64_t>(1, lanes / 8);
       if ((e = launch_swarm_real(h->d_desc, d.precision, h->has_b, trace, ext, o.block_size, grid, o.pending_trigger, lds,
                                  ch_off, ll.cum_off, first, count, hc.dropped != 0 ? 1 : 0, park_in, n_parked, park_out,
-                                 park_min, park_lanes, queued, s)) != hipSuccess)
+                                 park_min, park_lanes, queued, s, team)) != hipSuccess)
         return hip_fail(e, "swarm kernel launch");
       h->n_launches += 1;
       if ((e = hipMemcpyAsync(&hc, d.ctr, sizeof(hc), hipMemcpyDeviceToHost, s)) != hipSuccess) return hip_fail(e, "counters");
@@ -815,7 +882,7 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
       count = tail - queued;
       queued = tail;
       n_parked = std::min<int64_t>(static_cast<int64_t>(hc.parked),
-                                   parked_capacity(static_cast<int64_t>(grid) * o.block_size, park_lanes));
+                                   parked_capacity(static_cast<int64_t>(grid) * (team.lanes > 1 ? team.block : o.block_size), park_lanes));
       h->n_parked += n_parked;
       std::swap(park_in, park_out);
     }

@@ -87,6 +87,13 @@ void make_items(const std::vector<int64_t>& n_e, const std::vector<int64_t>& n_c
                 std::vector<WorkItem>& items, int64_t slots, int64_t block,
                 const std::vector<double>* rank = nullptr);
 swarm_launch_opts resolve_opts(const swarm_launch_opts* o, int precision);
+// Whether the caller left the launch shape to the library.
+bool free_shape(const swarm_launch_opts* o);
+// Team shape of a launch whose electrons keep about `wide` of them running at once, at
+// `trials` trials per real collision.
+TeamShape team_shape(double wide, double trials);
+// The same for a launch of several instances (electrons, expected work per electron, trials).
+TeamShape team_shape(const std::vector<int64_t>& n_e, const std::vector<int64_t>& work, const std::vector<double>& trials);
 // Builds a swarm handle (validation, tables); with `mem` every device allocation of the
 // handle comes from that caller-owned region.
 swarm_status create_swarm(const swarm_component* comps, int32_t n_comps, const swarm_params* params,
@@ -122,6 +129,7 @@ struct swarm {
   double kernel_ms = 0.0, total_ms = 0.0;
   int64_t n_launches = 0, n_parked = 0;     // the last run's simulation launches, parked electrons
   swarm_launch_opts opts{};
+  bool free_shape = true;                   // no launch shape was asked for
   // a run started by swarm_run_async: 1 enqueued on the stream (dummy mode), 2 running on
   // `worker` (real mode, whose generations need the host between launches)
   int in_flight = 0;

@@ -25,6 +25,7 @@ struct swarm_batch {
   std::vector<WorkItem> h_items;
   TallyPlan tally;
   swarm_launch_opts opts{};
+  TeamShape team;                // of the launch, where the caller left its shape free
   int grid = 1;
   size_t lds = 0;
   int ch_off = 0, pool_off = 0, cum_off = -1;
@@ -62,7 +63,7 @@ hipError_t enqueue(swarm_batch* b) {
   if ((e = launch_swarm_dummy(static_cast<const InstanceDesc*>(b->descs.p), static_cast<const WorkItem*>(b->items.p),
                               static_cast<int32_t>(b->h_items.size()), item_counter(b), b->precision, b->magnetic,
                               false, b->extended, b->opts.service_waves, b->opts.block_size, b->grid,
-                              b->opts.pending_trigger, b->lds, b->ch_off, b->pool_off, b->cum_off, b->stream)) != hipSuccess)
+                              b->opts.pending_trigger, b->lds, b->ch_off, b->pool_off, b->cum_off, b->stream, b->team)) != hipSuccess)
     return e;
   return b->tally.launch(static_cast<const InstanceDesc*>(b->descs.p), b->stream);
 }
@@ -81,6 +82,10 @@ hipError_t capture(swarm_batch* b) {
   if (e != hipSuccess) return e;
   return hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
 }
+
+// Electrons of a work item at most, and its unit: one electron per lane, or per team.
+int64_t item_unit(const swarm_batch* b) { return b->team.lanes > 1 ? b->team.per_group() : b->opts.block_size; }
+int64_t item_size(const swarm_batch* b) { return b->team.lanes > 1 ? b->team.per_group() : b->opts.chunk; }
 
 // Upload the work items and size the grid to them.
 hipError_t upload_items(swarm_batch* b, int per_cu) {
@@ -107,7 +112,7 @@ hipError_t reorder(swarm_batch* b) {
     rank[i] = static_cast<double>(b->nc[i]) * (reals > 0 ? trials / reals + 3.0 : 4.0);
   }
   std::vector<WorkItem> items;
-  make_items(b->ne, b->nc, b->opts.chunk, items, b->slots, b->opts.block_size, &rank);
+  make_items(b->ne, b->nc, item_size(b), items, b->slots, item_unit(b), &rank);
   const bool same = items.size() == b->h_items.size() &&
                     std::equal(items.begin(), items.end(), b->h_items.begin(), [](const WorkItem& x, const WorkItem& y) {
                       return x.inst == y.inst && x.first == y.first && x.count == y.count;
@@ -189,12 +194,19 @@ swarm_status swarm_batch_create(swarm_t* handles, const swarm_job* jobs, int32_t
   b->ch_off = ll.ch_off;
   b->pool_off = ll.pool_off;
   b->cum_off = ll.cum_off;
-  const int per_cu = swarm_kernel_max_blocks_per_cu(b->precision, b->magnetic, false, false, b->extended,
-                                                    b->opts.service_waves, b->opts.block_size, b->lds);
+  if (free_shape(opts)) {
+    std::vector<double> trials;
+    for (const swarm* h : b->hs) trials.push_back(h->desc.trials);
+    b->team = team_shape(ne, nc, trials);
+  }
+  const int per_cu = b->team.lanes > 1
+      ? swarm_kernel_max_blocks_per_cu(b->precision, b->magnetic, false, false, b->extended, 0, b->team.block, b->lds, true)
+      : swarm_kernel_max_blocks_per_cu(b->precision, b->magnetic, false, false, b->extended, b->opts.service_waves,
+                                       b->opts.block_size, b->lds);
   b->slots = static_cast<int64_t>(device_info().n_cu) * per_cu;
   b->ne = ne;
   b->nc = nc;
-  make_items(ne, nc, b->opts.chunk, b->h_items, b->slots, b->opts.block_size);
+  make_items(ne, nc, item_size(b.get()), b->h_items, b->slots, item_unit(b.get()));
   if ((e = b->descs.ensure(n * sizeof(InstanceDesc))) != hipSuccess) return hip_fail(e, "descriptors");
   if ((e = hipMemcpyAsync(b->descs.p, b->h_descs.data(), n * sizeof(InstanceDesc), hipMemcpyHostToDevice, b->stream)) != hipSuccess ||
       (e = upload_items(b.get(), per_cu)) != hipSuccess)

@@ -172,7 +172,11 @@ struct InstanceDesc {
   double rel_kEc, rel_kBx, rel_kBz;       // relativistic mover in E and B: generator and
   double rel_l1, rel_l2, rel_p1, rel_p2, rel_K;   // field invariants
   int32_t built_ok;           // 1 after a successful build, -1 if a node has zero rate
-  int32_t pad_;
+  // Lowest node at which an electron of that energy loses at least what the field gives it
+  // (the host sets it to the top node, the build lowers it), and the trials per real collision
+  // there.  They shape launches only; no result depends on them.
+  uint32_t balance_node;
+  double trials;
 };
 
 struct WorkItem {
@@ -189,16 +193,27 @@ struct TallyTile {
   int64_t count;
 };
 
+// Launch shape of the team kernels: `lanes` lanes per electron (a power of two up to 32; 1: the
+// one-lane kernels, and the other fields are not used), `per_wave` teams in every wave (its
+// other lanes stay idle), work-groups of `block`, and the waiting lanes, in 64ths of a wave's
+// running ones, at which it serves collisions.
+struct TeamShape {
+  int lanes = 1, per_wave = 64, block = 64, trigger = 48;
+  int64_t per_group() const { return static_cast<int64_t>(per_wave) * (block / 64); }   // electrons at once
+};
+
 // Launchers implemented in swarm_kernels.hip.
 hipError_t launch_build(InstanceDesc* d_desc, const InstanceDesc& h_desc, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_mark_empty(swarm_record* r, int64_t n, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t* p, uint64_t v, int64_t n, hipStream_t s);
-// service_waves > 0 (and no trace): the pooled schedule, pool at LDS offset pool_off.
+// service_waves > 0 (and no trace): the pooled schedule, pool at LDS offset pool_off.  A team
+// launch of one instance may leave d_items NULL: n_items ranges of team.per_group() electrons.
 hipError_t launch_swarm_dummy(const InstanceDesc* d_desc, const WorkItem* d_items, int32_t n_items,
                               int32_t* d_item_counter, int precision, bool has_b, bool trace,
                               int ext, int service_waves, int block_size, int grid, int pending_trigger,
-                              size_t lds_bytes, int ch_off, int pool_off, int cum_off, hipStream_t s);
+                              size_t lds_bytes, int ch_off, int pool_off, int cum_off, hipStream_t s,
+                              TeamShape team);
 size_t swarm_pool_slot_bytes(int precision);
 // One real-secondaries launch: the n_park_in electrons in park_in (parked by the launch
 // before), then `count` electrons from `first` (the primaries if first < 0, else queued
@@ -211,13 +226,13 @@ hipError_t launch_swarm_real(const InstanceDesc* d_desc, int precision, bool has
                              int ext, int block_size, int grid, int pending_trigger, size_t lds_bytes,
                              int ch_off, int cum_off, int64_t first, int64_t count, int flush,
                              const ParkedState* park_in, int64_t n_park_in, ParkedState* park_out,
-                             int64_t park_min, int park_lanes, int64_t tail0, hipStream_t s);
+                             int64_t park_min, int park_lanes, int64_t tail0, hipStream_t s, TeamShape team);
 hipError_t launch_tallies(const InstanceDesc* d_desc, const TallyTile* d_tiles, int32_t n_tiles,
                           const int32_t* d_tile_base, const int64_t* d_nrec, int32_t n_inst,
                           double* d_part1, double* d_part2, double* d_tot1,
                           swarm_tallies_t* d_out, hipStream_t s);
 int swarm_kernel_max_blocks_per_cu(int precision, bool has_b, bool trace, bool real, int ext,
                                    int service_waves, int block_size,
-                                   size_t lds_bytes);
+                                   size_t lds_bytes, bool team = false);
 
 }  // namespace swarm_impl

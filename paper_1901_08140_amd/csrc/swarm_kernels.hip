@@ -312,17 +312,28 @@ __global__ void k_build_rates(InstanceDesc* desc) {
   const double ej = eps * kQe;
   const double speed = d.relativistic ? sqrt(2.0 * ej / kMe * (1.0 + ej / (2.0 * kMe * kC * kC))) / (1.0 + ej / (kMe * kC * kC))
                                       : sqrt(2.0 * ej / kMe);
-  double acc = 0.0;
+  double acc = 0.0, loss = 0.0;
   for (int c = 0; c < d.nc; ++c) {
     const int comp = d.raw_comp[c];
+    const double before = acc;
     const double dens = d.comp_frac[comp] * d.N;
     // eq. frequency: nu_c = n_k sigma_c(eps) v, eps in joule, v = sqrt(2 eps / m); the
     // relativistic mover takes the true speed |u|/gamma, |u| = sqrt(2 eps/m (1 + eps/(2 m c^2)))
     // the proper speed and gamma = 1 + eps/(m c^2)
     acc += dens * sigma_ext(d, c, eps) * speed;
     d.cum_cm[static_cast<size_t>(c) * d.G + g] = acc;
+    const double lost = d.raw_kind[c] == SWARM_ATTACHMENT ? eps
+                      : (d.raw_kind[c] == SWARM_ELASTIC ? 0.0 : d.raw_thr[c]) + 2.0 * kMe / (d.comp_mass_amu[comp] * kAmu) * eps;
+    loss += (acc - before) * lost;
   }
   d.nodes[g] = eps;
+  // Energy balance (eV/s): the heating of an electron that collides at the rate acc, along B
+  // and across it, against its mean loss in collisions.  Electrons live around the lowest
+  // energy where the loss prevails.
+  const double w = kQe * d.B / kMe, cb = cos(d.B_angle), sb = sin(d.B_angle);
+  const double heat = kQe * d.E * d.E / kMe *
+                      (d.B > 0.0 ? cb * cb / acc + sb * sb * acc / (acc * acc + w * w) : 1.0 / acc);
+  if (loss >= heat) atomicMin(&desc->balance_node, static_cast<uint32_t>(g));
 }
 
 // Pairs (F[g], F[g+1]-F[g]) of every running sum (node major) and of the total rate.  The
@@ -416,6 +427,13 @@ __global__ void k_build_constants(InstanceDesc* desc) {
     }
     d.built_ok = ok;
     d.majorant = nup;
+    // The energies spread around the balance node, most of them to lower rates: over gases and
+    // fields the trials per real collision beyond the first are about 1.5 times those at the
+    // node (argon 100 Td: 2.3 counted, 1.4 at the node; Ar:CO2 31 Td: 3.2 and 1.8; 93:7 at
+    // 2.4 Td: 22.7 and 21).  The adaptive strategies make about 2, and with the
+    // returns to the last collision after fails their runs behave like 4.
+    d.trials = 1.0 + 1.5 * (nup / F[min(d.balance_node, static_cast<uint32_t>(d.G - 1))] - 1.0);
+    if (d.trial_strategy != SWARM_TRIAL_CONSTANT) d.trials = fmin(d.trials, 4.0);
     d.inv_majorant = 1.0 / nup;
     d.majorant_f = static_cast<float>(nup);
     d.cT_f = static_cast<float>(kLn2 / nup);
@@ -1327,6 +1345,54 @@ __device__ __forceinline__ int first_channel_below(const Consts<R>& C, const typ
 }
 enum : int { RC_CONTINUE = 0, RC_STOP = 1 };
 
+// A lane's place in its team (see k_swarm_team): g lanes from lane `base` on, this one the
+// sub-th.  One lane by itself: g = 1.
+struct TeamLane {
+  int g, sub, base;
+};
+
+// The bits of a wave mask that belong to the lane's team, from bit 0.
+__device__ __forceinline__ uint32_t team_bits(uint64_t mask, const TeamLane& t) {
+  return static_cast<uint32_t>(mask >> t.base) & (0xffffffffu >> (32 - t.g));
+}
+
+// Channel of a candidate by a whole team: the running sums of the row are compared by its
+// lanes, up to four each, in one memory round trip (bisection takes one per halving, and a
+// lone wave waits for each).  The answer is the one-lane kernel's to the bit: the first c
+// with x < C_c for few channels, else what bisection gives, which differs only where the
+// rounding of the interpolated sums makes them decrease; the few comparisons are then
+// bisected in registers.
+template <typename R>
+__device__ __forceinline__ int team_channel(const Consts<R>& C, const typename Pair<R>::T* row, R x, R w,
+                                            const TeamLane& t) {
+  using PT = typename Pair<R>::T;
+  int lo = 0, hi = C.nc - 1;
+  const int at_once = min(4 * t.g, 64);
+  while (C.nc > kScanChannels && hi - lo > at_once) {
+    const int mid = (lo + hi) >> 1;
+    if (x < lerp_pair(row[mid], w)) hi = mid; else lo = mid + 1;
+  }
+  const int n = hi - lo;
+  if (n == 0) return lo;
+  PT q[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) q[i] = row[lo + min(i * t.g + t.sub, n - 1)];
+  uint64_t below = 0;          // bit i: x < C_(lo + i)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t b = team_bits(__ballot(i * t.g + t.sub < n && x < lerp_pair(q[i], w)), t);
+    if (i * t.g < 64) below |= b << (i * t.g);
+  }
+  const int z = below != 0 ? __ffsll(static_cast<long long>(below)) - 1 : n;
+  if (C.nc <= kScanChannels || z == n || (below >> z) == (~0ull >> (64 - (n - z)))) return lo + z;
+  int a = 0, b = n;
+  while (a < b) {
+    const int mid = (a + b) >> 1;
+    if ((below >> mid) & 1ull) b = mid; else a = mid + 1;
+  }
+  return lo + a;
+}
+
 // Moving targets (section "Effect of gas temperature").  The target velocity of collision k
 // has three normal components of spread sqrt(kT/M), from the four uniforms of the THERMAL
 // block by Box-Muller.  moving_target() returns the centre-of-momentum velocity Vcm = (m V1 +
@@ -1456,10 +1522,11 @@ __device__ __forceinline__ int forbidden_pick(const InstanceDesc& d, Lane<R>& L,
 // check, isotropic scattering with Fraser-Mathieson energy transfer, ionisation and
 // attachment, then the anchor moves to the collision point.  Returns RC_STOP when the
 // electron has reached its stop count or was removed.
-template <typename R, bool HB, bool TR, bool REAL, int EXT>
+// With TEAM the lanes of a team make the collision together, all with the same operands.
+template <typename R, bool HB, bool TR, bool REAL, int EXT, bool TEAM = false>
 __device__ __forceinline__ int real_collision(const InstanceDesc& d, Lane<R>& L, const Consts<R>& C,
                                               const typename Pair<R>::T* __restrict__ s_nu,
-                                              bool* spawn) {
+                                              bool* spawn, TeamLane team = {1, 0, 0}) {
   *spawn = false;
   const R eps = L.p_eps;
   const R x = L.p_x;
@@ -1488,8 +1555,11 @@ __device__ __forceinline__ int real_collision(const InstanceDesc& d, Lane<R>& L,
   const R w = over ? R(0) : L.p_w;
   const typename Pair<R>::T* row = C.cum + gi * C.nc;   // (G+1) nc < 2^31: a 32-bit offset
   int lo;
+  if constexpr (TEAM) draw_scattering<R>(L, C);   // under the row's memory round trip
   if (C.nc == 1) {
     lo = 0;
+  } else if (TEAM && C.nc > kScanChannels) {
+    lo = team_channel<R>(C, row, x, w, team);
   } else if (C.nc <= 5) {
     lo = first_channel_below<R, 4>(C, row, x, w);     // the argon-like gas: 5 channels
   } else if (C.nc <= kScanChannels) {
@@ -1530,7 +1600,7 @@ __device__ __forceinline__ int real_collision(const InstanceDesc& d, Lane<R>& L,
     if (e64 < ch.onset) return forbidden_pick<R, TR, EXT>(d, L, C, lo, eps, nu_eps);
   }
   if (over) L.nover += 1;
-  draw_scattering<R>(L, C);   // scattering block k (kept in the lane for a secondary)
+  if constexpr (!TEAM) draw_scattering<R>(L, C);   // scattering block k (kept in the lane for a secondary)
   const W4 h = L.sh;
   const W4 l = L.sl;
   R nx, ny, nz;
@@ -1781,6 +1851,211 @@ __global__ void __launch_bounds__(512) k_swarm_dummy(const InstanceDesc* __restr
           if (d.saved != nullptr) d.saved[L.rec].started = 2u;
         } else {
           save_state<R, EXT>(d, L, C, L.rec);
+        }
+        L.state = ST_IDLE;
+      }
+      if (__ballot(L.state != ST_DONE) == 0) break;
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// Team kernel: g lanes (a power of two) run one electron together.  Used when a launch holds
+// too few electrons to fill the device with one per lane; a lone wave is then bound by the
+// length of an electron's chain of dependent steps, not by issue slots.  Every lane of a team
+// holds the electron's whole state.  The team's lanes draw the next g random-number blocks at
+// once (lane j the block L.block + j) and test their 2 g trials together; the first hit in
+// stream order is the electron's next candidate and the blocks behind it are dropped, exactly
+// as if they had never been drawn (they are drawn again, with the same counters, after the
+// collision).  The flight time still grows trial by trial in stream order, with the roundings
+// of the one-lane kernel, through a chain of lane shifts.  The collision runs on all lanes of
+// the team with the same operands, so no state has to be exchanged; only the team's first
+// lane claims electrons and stores.
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ float lane_shift_up(float x) {      // lane i <- lane i - 1
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double lane_shift_up(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x138, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x138, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
+// A trial's energy, null test and table position at flight time T (see one_trial).
+template <typename R> struct TrialPoint { R T, eps, x, w; int gi; bool hit; };
+template <typename R, bool HB, int EXT>
+__device__ __forceinline__ TrialPoint<R> trial_point(const Lane<R>& L, const Consts<R>& C,
+                                                     const typename Pair<R>::T* __restrict__ s_nu, R T,
+                                                     uint32_t hr, uint32_t lr) {
+  TrialPoint<R> t;
+  t.T = T;
+  if constexpr (sizeof(R) == 4) t.x = static_cast<float>(hr >> 8) * (EXT ? L.nup24 : C.nup24);
+  else t.x = uni(hr, lr, R(0)) * (EXT ? L.nup : C.nup);
+  t.eps = energy_at<R, HB, EXT>(L, C, T);
+  const R nu = lds_rate<!HB && EXT == 0>(s_nu, t.eps, C, &t.gi, &t.w);
+  t.hit = t.x < nu;
+  return t;
+}
+
+template <typename R, bool HB, int EXT>
+__device__ __forceinline__ void team_blocks(Lane<R>& L, const Consts<R>& C,
+                                            const typename Pair<R>::T* __restrict__ s_nu, const TeamLane& t) {
+  const uint32_t blk = L.block + static_cast<uint32_t>(t.sub);
+  const W4 h = draw_trial(C.key, L.pre_hi, blk);
+  W4 l = {0, 0, 0, 0};
+  if constexpr (sizeof(R) == 8) l = draw_trial(C.key, L.pre_lo, blk);
+  const R cT = EXT ? L.cT : C.cT;
+  R fa, fb;      // the two flight-time increments (FP32: their logarithms)
+  if constexpr (sizeof(R) == 4) {
+    fa = __builtin_amdgcn_logf(fmaf(static_cast<float>(h.x >> 8), -0x1.0p-24f, 1.0f));
+    fb = __builtin_amdgcn_logf(fmaf(static_cast<float>(h.z >> 8), -0x1.0p-24f, 1.0f));
+  } else {
+    fa = flight(one_minus_uni(h.x, l.x), cT, C.logtab);
+    fb = flight(one_minus_uni(h.z, l.z), cT, C.logtab);
+  }
+  R Tin = L.T, Ta, Tb;
+  for (int j = 1;; ++j) {
+    if constexpr (sizeof(R) == 4) {
+      Ta = fmaf(fa, -cT, Tin);
+      Tb = fmaf(fb, -cT, Ta);
+    } else {
+      Ta = Tin + fa;
+      Tb = Ta + fb;
+    }
+    if (j == t.g) break;
+    const R up = lane_shift_up(Tb);
+    Tin = t.sub == 0 ? L.T : up;     // right for the lanes sub <= j
+  }
+  const TrialPoint<R> a = trial_point<R, HB, EXT>(L, C, s_nu, Ta, h.y, l.y);
+  const TrialPoint<R> b = trial_point<R, HB, EXT>(L, C, s_nu, Tb, h.w, l.w);
+  const uint32_t hits = team_bits(__ballot(a.hit || b.hit), t);
+  if (hits != 0) {
+    const int j = __ffs(static_cast<int>(hits)) - 1;
+    const int src = t.base + j;
+    L.T = __shfl(a.hit ? a.T : b.T, src);
+    L.p_eps = __shfl(a.hit ? a.eps : b.eps, src);
+    L.p_x = __shfl(a.hit ? a.x : b.x, src);
+    L.p_w = __shfl(a.hit ? a.w : b.w, src);
+    L.p_gi = __shfl(a.hit ? a.gi : b.gi, src);
+    L.p_sub = static_cast<uint32_t>(__shfl(a.hit ? 0 : 1, src));
+    L.block += static_cast<uint32_t>(j) + 1u;
+    if (EXT && C.variable) L.grace -= 2u * static_cast<uint32_t>(j) + L.p_sub + 1u;
+    L.state = ST_READY;
+  } else {
+    L.T = __shfl(Tb, t.base + t.g - 1);
+    L.block += static_cast<uint32_t>(t.g);
+    if (EXT && C.variable) L.grace -= 2u * static_cast<uint32_t>(t.g);
+  }
+}
+
+// One step of a team: the next g blocks, or near the block cap, and where nu' of an adaptive
+// strategy may be renewed within the team's trials, one block (every lane the same one).
+template <typename R, bool HB, int EXT>
+__device__ __forceinline__ void team_trials(Lane<R>& L, const Consts<R>& C,
+                                            const typename Pair<R>::T* __restrict__ s_nu, const TeamLane& t) {
+  if (L.block >= kMaxBlocks - 64u || (EXT && C.variable && L.grace <= 2u * static_cast<uint32_t>(t.g)))
+    trial_block<R, HB, EXT>(L, C, s_nu);
+  else
+    team_blocks<R, HB, EXT>(L, C, s_nu, t);
+}
+
+template <typename R, bool HB, int EXT>
+__global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restrict__ descs,
+                                                    const WorkItem* __restrict__ items, int n_items,
+                                                    int* __restrict__ item_ctr, int pend_trig, int ch_off,
+                                                    int cum_off, int g, int per_wave, int64_t chunk) {
+  using PT = typename Pair<R>::T;
+  extern __shared__ __align__(16) unsigned char smem[];
+  PT* s_nu = reinterpret_cast<PT*>(smem);
+  __shared__ double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
+  ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
+  __shared__ int s_item;
+  __shared__ int s_next;
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  const TeamLane team = {g, lane & (g - 1), lane & ~(g - 1)};
+  int cur_inst = -1;
+  for (;;) {
+    if (threadIdx.x == 0) s_item = atomicAdd(item_ctr, 1);
+    __syncthreads();
+    const int it = __builtin_amdgcn_readfirstlane(s_item);
+    if (it >= n_items) break;
+    // without a list, the electrons of one instance in ranges of `chunk`
+    WorkItem wi;
+    if (items != nullptr) wi = items[it];
+    else wi = {0, 0, it * chunk, min(chunk, descs->n_electrons - it * chunk)};
+    const int inst = __builtin_amdgcn_readfirstlane(wi.inst);
+    const InstanceDesc& d = descs[inst];
+    if (inst != cur_inst) {
+      const PT* src = reinterpret_cast<const PT*>(sizeof(R) == 8 ? static_cast<const void*>(d.nu64)
+                                                                 : static_cast<const void*>(d.nu32));
+      for (int i = threadIdx.x; i <= d.G; i += blockDim.x) {
+        PT q = src[i > 0 ? i - 1 : 0];
+        if (i == 0) q.y = 0;
+        s_nu[i] = q;
+      }
+      for (int c = threadIdx.x; c < d.nc; c += blockDim.x) s_ch[c] = d.chan[c];
+      if constexpr (sizeof(R) == 8)
+        for (int j = threadIdx.x; j < kUnitLogStride * kUnitLogEntries; j += blockDim.x) s_logtab[j] = d.logtab[j];
+      stage_cum<R>(d, smem, cum_off);
+      cur_inst = inst;
+    }
+    if (threadIdx.x == 0) s_next = 0;
+    __syncthreads();
+    Consts<R> C = load_consts<R>(d);
+    C.chan = s_ch;
+    C.logtab = s_logtab;
+    if (cum_off >= 0) {
+      C.cum = reinterpret_cast<const PT*>(smem + cum_off);
+      C.cum_lds = true;
+    }
+    const int64_t count = wi.count;
+    Lane<R> L;
+    L.state = team.base < per_wave * g ? ST_IDLE : ST_DONE;
+    L.trace_slot = -1;
+    L.n_ev = 0;
+    for (;;) {
+      if (L.state == ST_IDLE) {
+        int e = 0;
+        if (team.sub == 0) e = atomicAdd(&s_next, 1);
+        e = __shfl(e, team.base);
+        if (e < count) {
+          const int64_t ei = wi.first + e;
+          const uint32_t started = d.saved != nullptr ? d.saved[ei].started : 0u;
+          if (started != 2u) {          // 2: finished in an earlier launch
+            L.rec = ei;
+            if (started == 1u) load_state<R, HB, EXT>(d, L, C, ei);
+            else init_primary<R, HB, EXT>(L, C, s_nu, static_cast<uint64_t>(ei));
+            L.k_stop = stop_count(L.k, C);
+            L.state = ST_ACTIVE;
+          }
+        } else {
+          L.state = ST_DONE;
+        }
+      }
+      bool drawing = L.state == ST_ACTIVE;
+      const int trig = wave_trigger(drawing, pend_trig);
+      for (;;) {
+        if (drawing) team_trials<R, HB, EXT>(L, C, s_nu, team);
+        drawing = L.state == ST_ACTIVE;
+        const uint64_t ready = __ballot(L.state == ST_READY);
+        if (__ballot(drawing) == 0 || static_cast<int>(__popcll(ready)) >= trig) break;
+      }
+      if (L.state == ST_READY) {
+        bool spawn;
+        if (real_collision<R, HB, false, false, EXT, true>(d, L, C, s_nu, &spawn, team) == RC_STOP) L.state = ST_STOPPED;
+      }
+      if (L.state == ST_STOPPED) {
+        const bool final = L.k >= C.n_coll || (L.flags & 4u);
+        if (L.k >= C.n_coll) L.flags |= 1u;
+        if (team.sub == 0) {
+          if (final) {
+            write_record(d, L);
+            atomicAdd(reinterpret_cast<unsigned long long*>(&d.ctr->n_done), 1ull);
+            if (d.saved != nullptr) d.saved[L.rec].started = 2u;
+          } else {
+            save_state<R, EXT>(d, L, C, L.rec);
+          }
         }
         L.state = ST_IDLE;
       }
@@ -2105,12 +2380,13 @@ __device__ __forceinline__ int64_t wave_uniform(int64_t x) {
   return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
-template <typename R, bool HB, bool TR, int EXT>
+template <typename R, bool HB, bool TR, int EXT, bool TEAM>
 __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restrict__ desc, int pend_trig,
                                                     int ch_off, int cum_off, int64_t first, int64_t count,
                                                     int flush, const ParkedState* __restrict__ park_in,
                                                     int64_t n_park_in, ParkedState* __restrict__ park_out,
-                                                    int64_t park_min, int park_lanes, int64_t tail0) {
+                                                    int64_t park_min, int park_lanes, int64_t tail0,
+                                                    int g, int per_wave) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
@@ -2142,10 +2418,16 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
   const int64_t N = d.n_electrons;
   const int64_t child_cap = d.capacity - N;
   Lane<R> L;
-  L.state = ST_IDLE;
+  TeamLane team = {1, 0, static_cast<int>(__lane_id())};
+  if constexpr (TEAM) team = {g, team.base & (g - 1), team.base & ~(g - 1)};
+  L.state = !TEAM || team.base < per_wave * g ? ST_IDLE : ST_DONE;
   L.trace_slot = -1;
   L.n_ev = 0;
-  const uint64_t lane_lt = (1ull << __lane_id()) - 1ull;
+  // lanes that claim and store: all of them, or the first of every team; and those before this
+  // lane's electron
+  const uint64_t firsts = TEAM ? __ballot(team.sub == 0) : ~0ull;
+  const uint64_t lane_lt = ((1ull << team.base) - 1ull) & firsts;
+  const int64_t claim = TEAM ? per_wave : static_cast<int>(kClaimChunk);
   // wave-uniform: the wave's chunk [w_next, w_end), whether the generation is exhausted,
   // whether the run is stopping after an overflow, and the pass count
   const int64_t total = n_park_in + count;   // parked electrons first, then the generation's
@@ -2160,15 +2442,15 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
         unsigned long long base = 0;
         if (static_cast<int>(__lane_id()) == leader)
           base = atomicAdd(reinterpret_cast<unsigned long long*>(&ctr->gen_next),
-                           static_cast<unsigned long long>(kClaimChunk));
+                           static_cast<unsigned long long>(claim));
         w_next = wave_uniform(static_cast<int64_t>(__shfl(base, leader)));
-        w_end = min(w_next + static_cast<int64_t>(kClaimChunk), total);
+        w_end = min(w_next + claim, total);
         exhausted = w_next >= total;
       }
       const int64_t avail = max(w_end - w_next, int64_t{0});
       const int64_t rank = static_cast<int64_t>(__popcll(idle & lane_lt));
       const int64_t e = w_next + rank;
-      w_next = wave_uniform(min(w_end, w_next + static_cast<int64_t>(__popcll(idle))));
+      w_next = wave_uniform(min(w_end, w_next + static_cast<int64_t>(__popcll(idle & firsts))));
       if (L.state == ST_IDLE && exhausted && avail == 0) L.state = ST_DONE;
       if (L.state == ST_IDLE && rank < avail) {
         if (e < n_park_in) {
@@ -2218,8 +2500,8 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
     // and this launch has created enough secondaries for the next one.  The running lanes
     // stop at their next real collision (a ready lane at the one it is about to make).
     if (park_min > 0 && exhausted && !parking && !aborting && pass % kParkPoll == 0) {
-      const int running = static_cast<int>(__popcll(__ballot(L.state == ST_ACTIVE || L.state == ST_READY)));
-      if (running > 0 && running <= park_lanes) {
+      const int running = static_cast<int>(__popcll(__ballot(L.state == ST_ACTIVE || L.state == ST_READY) & firsts));
+      if (running > 0 && running * 64 <= park_lanes * (TEAM ? per_wave : 64)) {
         const int64_t made = wave_uniform(static_cast<int64_t>(__hip_atomic_load(
                                               &ctr->child_tail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) - tail0;
         if (made >= park_min) {
@@ -2230,16 +2512,21 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
     }
     uint64_t ready;
     bool drawing = L.state == ST_ACTIVE;
+    const int trig = TEAM ? wave_trigger(drawing, pend_trig) : pend_trig;
     for (;;) {
-      if (drawing) trial_block<R, HB, EXT>(L, C, s_nu);
+      if (drawing) {
+        if constexpr (TEAM) team_trials<R, HB, EXT>(L, C, s_nu, team);
+        else trial_block<R, HB, EXT>(L, C, s_nu);
+      }
       drawing = L.state == ST_ACTIVE;
       ready = __ballot(L.state == ST_READY);
-      if (__ballot(drawing) == 0 || static_cast<int>(__popcll(ready)) >= pend_trig) break;
+      if (__ballot(drawing) == 0 || static_cast<int>(__popcll(ready)) >= trig) break;
     }
     if (ready != 0) {
       bool spawn = false;
       if (L.state == ST_READY) {
-        if (real_collision<R, HB, TR, true, EXT>(d, L, C, s_nu, &spawn) == RC_STOP) L.state = ST_STOPPED;
+        if (real_collision<R, HB, TR, true, EXT, TEAM>(d, L, C, s_nu, &spawn, team) == RC_STOP) L.state = ST_STOPPED;
+        if constexpr (TEAM) spawn = spawn && team.sub == 0;
       }
       // append the secondaries of this wave: one reservation, ranks from the lane mask
       const uint64_t sm = __ballot(spawn);
@@ -2272,12 +2559,16 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
         // parked (not attached, capped or aborted): resumed by the next launch.  The slots
         // stay below parked_capacity of the launch's threads, which the host's buffers hold;
         // past that a lane would run on.
-        const uint64_t ps = atomicAdd(reinterpret_cast<unsigned long long*>(&ctr->parked), 1ull);
+        unsigned long long ps = 0;
+        if (!TEAM || team.sub == 0) ps = atomicAdd(reinterpret_cast<unsigned long long*>(&ctr->parked), 1ull);
+        if constexpr (TEAM) ps = __shfl(ps, team.base);
         if (ps < static_cast<uint64_t>(parked_capacity(static_cast<int64_t>(gridDim.x) * blockDim.x, park_lanes))) {
-          ParkedState p;
-          p.s = saved_of<R, EXT>(L, C);
-          p.rec = L.rec;
-          park_out[ps] = p;
+          if (!TEAM || team.sub == 0) {
+            ParkedState p;
+            p.s = saved_of<R, EXT>(L, C);
+            p.rec = L.rec;
+            park_out[ps] = p;
+          }
           L.state = ST_DONE;
         } else {
           L.k_stop = C.n_coll;
@@ -2286,7 +2577,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
         }
       } else {
         if (L.k >= C.n_coll && !(L.flags & 10u)) L.flags |= 1u;   // attached or aborted: not finished
-        write_record(d, L);
+        if (!TEAM || team.sub == 0) write_record(d, L);
         L.state = ST_IDLE;
       }
     }
@@ -2515,11 +2806,24 @@ void* dummy_fn(int ext) {
        : ext == 1 ? reinterpret_cast<void*>(&k_swarm_dummy<R, HB, TR, 1>)
                   : reinterpret_cast<void*>(&k_swarm_dummy<R, HB, TR, 0>);
 }
-template <typename R, bool HB, bool TR>
+template <typename R, bool HB, bool TR, bool TEAM = false>
 void* real_fn(int ext) {
-  return ext == 2 ? reinterpret_cast<void*>(&k_swarm_real<R, HB, TR, 2>)
-       : ext == 1 ? reinterpret_cast<void*>(&k_swarm_real<R, HB, TR, 1>)
-                  : reinterpret_cast<void*>(&k_swarm_real<R, HB, TR, 0>);
+  return ext == 2 ? reinterpret_cast<void*>(&k_swarm_real<R, HB, TR, 2, TEAM>)
+       : ext == 1 ? reinterpret_cast<void*>(&k_swarm_real<R, HB, TR, 1, TEAM>)
+                  : reinterpret_cast<void*>(&k_swarm_real<R, HB, TR, 0, TEAM>);
+}
+
+template <typename R, bool HB>
+void* team_fn(int ext, bool real) {
+  if (real) return real_fn<R, HB, false, true>(ext);
+  return ext == 2 ? reinterpret_cast<void*>(&k_swarm_team<R, HB, 2>)
+       : ext == 1 ? reinterpret_cast<void*>(&k_swarm_team<R, HB, 1>)
+                  : reinterpret_cast<void*>(&k_swarm_team<R, HB, 0>);
+}
+
+void* pick_team(int precision, bool has_b, int ext, bool real) {
+  if (precision == SWARM_FP32_MIXED) return has_b ? team_fn<float, true>(ext, real) : team_fn<float, false>(ext, real);
+  return has_b ? team_fn<double, true>(ext, real) : team_fn<double, false>(ext, real);
 }
 
 template <typename R, bool HB>
@@ -2591,13 +2895,20 @@ size_t swarm_pool_slot_bytes(int precision) {
 hipError_t launch_swarm_dummy(const InstanceDesc* d_desc, const WorkItem* d_items, int32_t n_items,
                               int32_t* d_item_counter, int precision, bool has_b, bool trace,
                               int ext, int service_waves, int block_size, int grid, int pending_trigger,
-                              size_t lds_bytes, int ch_off, int pool_off, int cum_off, hipStream_t s) {
+                              size_t lds_bytes, int ch_off, int pool_off, int cum_off, hipStream_t s, TeamShape team) {
   if (service_waves > 0 && !trace) {
     if (service_waves >= block_size / 64) return hipErrorInvalidValue;
     void* fn = pick_pooled(precision, has_b, ext);
     void* args[] = {const_cast<InstanceDesc**>(&d_desc), const_cast<WorkItem**>(&d_items), &n_items,
                     &d_item_counter, &service_waves, &ch_off, &pool_off, &cum_off};
     return hipLaunchKernel(fn, dim3(grid), dim3(block_size), args, lds_bytes, s);
+  }
+  if (team.lanes > 1 && !trace) {
+    int64_t chunk = team.per_group();
+    void* fn = pick_team(precision, has_b, ext, false);
+    void* args[] = {const_cast<InstanceDesc**>(&d_desc), const_cast<WorkItem**>(&d_items), &n_items,
+                    &d_item_counter, &team.trigger, &ch_off, &cum_off, &team.lanes, &team.per_wave, &chunk};
+    return hipLaunchKernel(fn, dim3(grid), dim3(team.block), args, lds_bytes, s);
   }
   void* fn = pick_kernel(precision, has_b, trace, false, ext);
   void* args[] = {const_cast<InstanceDesc**>(&d_desc), const_cast<WorkItem**>(&d_items), &n_items,
@@ -2609,10 +2920,16 @@ hipError_t launch_swarm_real(const InstanceDesc* d_desc, int precision, bool has
                              int ext, int block_size, int grid, int pending_trigger, size_t lds_bytes,
                              int ch_off, int cum_off, int64_t first, int64_t count, int flush,
                              const ParkedState* park_in, int64_t n_park_in, ParkedState* park_out,
-                             int64_t park_min, int park_lanes, int64_t tail0, hipStream_t s) {
-  void* fn = pick_kernel(precision, has_b, trace, true, ext);
+                             int64_t park_min, int park_lanes, int64_t tail0, hipStream_t s, TeamShape team) {
+  const bool teams = team.lanes > 1 && !trace;
+  void* fn = teams ? pick_team(precision, has_b, ext, true) : pick_kernel(precision, has_b, trace, true, ext);
+  if (teams) {
+    block_size = team.block;
+    pending_trigger = team.trigger;
+  }
   void* args[] = {const_cast<InstanceDesc**>(&d_desc), &pending_trigger, &ch_off, &cum_off, &first, &count, &flush,
-                  const_cast<ParkedState**>(&park_in), &n_park_in, &park_out, &park_min, &park_lanes, &tail0};
+                  const_cast<ParkedState**>(&park_in), &n_park_in, &park_out, &park_min, &park_lanes, &tail0,
+                  &team.lanes, &team.per_wave};
   return hipLaunchKernel(fn, dim3(grid), dim3(block_size), args, lds_bytes, s);
 }
 
@@ -2630,9 +2947,10 @@ hipError_t launch_tallies(const InstanceDesc* d_desc, const TallyTile* d_tiles, 
 }
 
 int swarm_kernel_max_blocks_per_cu(int precision, bool has_b, bool trace, bool real, int ext,
-                                   int service_waves, int block_size, size_t lds_bytes) {
+                                   int service_waves, int block_size, size_t lds_bytes, bool team) {
   int n = 0;
-  void* fn = service_waves > 0 && !trace && !real ? pick_pooled(precision, has_b, ext)
+  void* fn = team ? pick_team(precision, has_b, ext, real)
+           : service_waves > 0 && !trace && !real ? pick_pooled(precision, has_b, ext)
                                                   : pick_kernel(precision, has_b, trace, real, ext);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn,
                                                    block_size, lds_bytes) != hipSuccess)

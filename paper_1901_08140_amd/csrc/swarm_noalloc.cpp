@@ -140,19 +140,24 @@ swarm_status swarm_run_noalloc(swarm_t h, int64_t n_electrons, int64_t n_collisi
   if (static_cast<int64_t>(ll.bytes) > device_info().lds_per_block)
     return fail(SWARM_ERR_INVALID_ARG, "the tables need %zu bytes of LDS per work-group", ll.bytes);
   const int ext = d.thermal_targets || d.relativistic ? 2 : d.trial_strategy != SWARM_TRIAL_CONSTANT ? 1 : 0;
-  const int per_cu = swarm_kernel_max_blocks_per_cu(d.precision, h->has_b, false, false, ext, o.service_waves,
-                                                    o.block_size, ll.bytes);
+  const TeamShape team = h->free_shape ? team_shape(static_cast<double>(n_electrons), d.trials) : TeamShape{};
+  const int per_cu = team.lanes > 1
+      ? swarm_kernel_max_blocks_per_cu(d.precision, h->has_b, false, false, ext, 0, team.block, ll.bytes, true)
+      : swarm_kernel_max_blocks_per_cu(d.precision, h->has_b, false, false, ext, o.service_waves, o.block_size, ll.bytes);
   const int64_t slots = static_cast<int64_t>(device_info().n_cu) * per_cu;
-  auto round_up = [&](int64_t n) { return (n + o.block_size - 1) / o.block_size * o.block_size; };
+  const int64_t unit = team.lanes > 1 ? team.per_group() : o.block_size;
+  auto round_up = [&](int64_t n) { return (n + unit - 1) / unit * unit; };
   int64_t chunk = round_up((n_electrons + 4 * slots - 1) / (4 * slots));
-  chunk = std::max<int64_t>(o.block_size, std::min<int64_t>(chunk, o.chunk));
-  chunk = std::max(chunk, round_up((n_electrons + kMaxItems - 1) / kMaxItems));   // at most kMaxItems items
+  chunk = team.lanes > 1 ? unit : std::max<int64_t>(o.block_size, std::min<int64_t>(chunk, o.chunk));
+  // a list of at most kMaxItems items (a team launch has none)
+  if (team.lanes == 1) chunk = std::max(chunk, round_up((n_electrons + kMaxItems - 1) / kMaxItems));
   const int64_t n_items = (n_electrons + chunk - 1) / chunk;
   const int64_t n_tiles = (n_electrons + kTallyTile - 1) / kTallyTile;
-  if (n_items > kMaxItems || n_tiles > kMaxTiles) return fail(SWARM_ERR_INVALID_ARG, "work does not fit the scratch");
-  const int64_t plan_n = std::max(n_items, n_tiles);
+  const int64_t n_listed = team.lanes > 1 ? 0 : n_items;
+  if (n_listed > kMaxItems || n_tiles > kMaxTiles) return fail(SWARM_ERR_INVALID_ARG, "work does not fit the scratch");
+  const int64_t plan_n = std::max(n_listed, n_tiles);
   hipLaunchKernelGGL(k_noalloc_plan, dim3(static_cast<unsigned>((plan_n + 255) / 256)), dim3(256), 0, s, d_items,
-                     static_cast<int32_t>(n_items), n_electrons, chunk, d_ctr, d_tiles, static_cast<int32_t>(n_tiles),
+                     static_cast<int32_t>(n_listed), n_electrons, chunk, d_ctr, d_tiles, static_cast<int32_t>(n_tiles),
                      d_base, d_nrec);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "plan launch");
   if ((e = launch_fill_u64(reinterpret_cast<uint64_t*>(d.ctr), 0ull, sizeof(RunCounters) / sizeof(uint64_t), s)) != hipSuccess)
@@ -161,9 +166,9 @@ swarm_status swarm_run_noalloc(swarm_t h, int64_t n_electrons, int64_t n_collisi
     return hip_fail(e, "descriptor");
   if ((e = hipEventRecord(h->ev[0], s)) != hipSuccess) return hip_fail(e, "event");
   const int grid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(n_items, slots)));
-  if ((e = launch_swarm_dummy(h->d_desc, d_items, static_cast<int32_t>(n_items), d_ctr, d.precision, h->has_b, false,
+  if ((e = launch_swarm_dummy(h->d_desc, team.lanes > 1 ? nullptr : d_items, static_cast<int32_t>(n_items), d_ctr, d.precision, h->has_b, false,
                               ext, o.service_waves, o.block_size, grid, o.pending_trigger, ll.bytes, ll.ch_off,
-                              ll.pool_off, ll.cum_off, s)) != hipSuccess)
+                              ll.pool_off, ll.cum_off, s, team)) != hipSuccess)
     return hip_fail(e, "swarm kernel launch");
   if ((e = hipEventRecord(h->ev[1], s)) != hipSuccess) return hip_fail(e, "event");
   if ((e = launch_tallies(h->d_desc, d_tiles, static_cast<int32_t>(n_tiles), d_base, d_nrec, 1, d_part1, d_part2,

@@ -357,6 +357,8 @@ void scheduler(swarm_server* s) {
     }
     descs.clear();
     std::vector<int64_t> ne, nc;
+    std::vector<int64_t> quanta;
+    std::vector<double> trials;
     int G = 0, n_ch = 0;
     bool magnetic = false;
     int extended = 0;
@@ -365,6 +367,8 @@ void scheduler(swarm_server* s) {
       d.quantum = static_cast<uint32_t>(std::min<int64_t>(r->quantum, 0xffffffffLL));
       descs.push_back(d);
       ne.push_back(r->n_e);
+      quanta.push_back(r->quantum);
+      trials.push_back(d.trials);
       // the items' order and sizes follow the expected device work per electron (longest
       // first), not the collision count: with per-request quanta the requests with the
       // fewest collisions per epoch are the slowest ones
@@ -382,12 +386,23 @@ void scheduler(swarm_server* s) {
     const swarm_launch_opts o = resolve_opts(&s->p.opts, s->p.precision);
     const LdsLayout ll = lds_layout(s->p.precision, G, n_ch, o.service_waves, o.table_layout);
     const size_t lds = ll.bytes;
-    const int per_cu = swarm_kernel_max_blocks_per_cu(s->p.precision, magnetic, false, false, extended,
-                                                      o.service_waves, o.block_size, lds);
-    make_items(ne, nc, o.chunk, items, static_cast<int64_t>(device_info().n_cu) * per_cu, o.block_size);
+    TeamShape team = free_shape(&s->p.opts) ? team_shape(ne, quanta, trials) : TeamShape{};
+    int per_cu = 1;
     hipError_t e;
-    bool ok = (e = s->descs.ensure(descs.size() * sizeof(InstanceDesc))) == hipSuccess &&
-              (e = s->items.ensure(items.size() * sizeof(WorkItem) + 256)) == hipSuccess;
+    bool ok = (e = s->descs.ensure(descs.size() * sizeof(InstanceDesc))) == hipSuccess;
+    for (;;) {
+      per_cu = team.lanes > 1
+          ? swarm_kernel_max_blocks_per_cu(s->p.precision, magnetic, false, false, extended, 0, team.block, lds, true)
+          : swarm_kernel_max_blocks_per_cu(s->p.precision, magnetic, false, false, extended, o.service_waves, o.block_size, lds);
+      const int64_t slots = static_cast<int64_t>(device_info().n_cu) * per_cu;
+      if (team.lanes > 1) make_items(ne, nc, team.per_group(), items, slots, team.per_group());
+      else make_items(ne, nc, o.chunk, items, slots, o.block_size);
+      if (ok) ok = (e = s->items.ensure(items.size() * sizeof(WorkItem) + 256)) == hipSuccess;
+      if (ok || e != hipErrorOutOfMemory || team.lanes == 1) break;
+      // a caller-owned region may hold the shorter list of the one-lane kernel only
+      team = TeamShape{};
+      ok = true;
+    }
     int32_t* item_ctr = ok ? reinterpret_cast<int32_t*>(static_cast<char*>(s->items.p) + items.size() * sizeof(WorkItem)) : nullptr;
     if (ok) ok = (e = hipMemcpyAsync(s->descs.p, descs.data(), descs.size() * sizeof(InstanceDesc), hipMemcpyHostToDevice, s->compute)) == hipSuccess &&
                  (e = hipMemcpyAsync(s->items.p, items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s->compute)) == hipSuccess &&
@@ -403,7 +418,7 @@ void scheduler(swarm_server* s) {
       ok = (e = launch_swarm_dummy(static_cast<const InstanceDesc*>(s->descs.p), static_cast<const WorkItem*>(s->items.p),
                                    static_cast<int32_t>(items.size()), item_ctr, s->p.precision, magnetic, false, extended,
                                    o.service_waves, o.block_size, grid, o.pending_trigger, lds, ll.ch_off,
-                                   ll.pool_off, ll.cum_off, s->compute)) == hipSuccess &&
+                                   ll.pool_off, ll.cum_off, s->compute, team)) == hipSuccess &&
            (e = hipEventRecord(ev1, s->compute)) == hipSuccess;
     }
     // while the epoch runs, prepare the requests that arrived meanwhile
