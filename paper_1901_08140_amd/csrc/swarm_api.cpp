@@ -405,7 +405,8 @@ swarm_launch_opts resolve_opts(const swarm_launch_opts* o, int precision) {
   r.use_graph = o ? o->use_graph : 0;
   r.block_size = std::max(64, std::min(1024, (r.block_size / 64) * 64));
   r.chunk = std::max(r.block_size, (r.chunk / r.block_size) * r.block_size);
-  r.pending_trigger = (o && o->pending_trigger) ? std::max(1, std::min(64, o->pending_trigger)) : 32;
+  // (0 stays: every instance's own number, from the trials its collisions take)
+  r.pending_trigger = o && o->pending_trigger ? std::max(1, std::min(64, o->pending_trigger)) : 0;
   r.service_waves = o ? std::max(0, std::min(r.block_size / 64 - 1, o->service_waves)) : 0;
   r.table_layout = (o && o->table_layout == 1) ? 1 : 0;
   r.park_lanes = (o && o->park_lanes) ? std::max(-1, std::min(64, o->park_lanes)) : kParkLanes;
@@ -609,12 +610,11 @@ static swarm_status build_swarm(swarm* h, const swarm_component* comps, int32_t 
   if (h->desc.built_ok != 1) return fail(SWARM_ERR_DEVICE, "table build did not complete");
   for (int i = 0; i < 3; ++i)
     if ((e = hipEventCreate(&h->ev[i])) != hipSuccess) return hip_fail(e, "hipEventCreate");
-  // Single runs default to work-groups of 128: a run of one swarm often holds fewer electrons
-  // than the GPU has lanes, and the smaller groups spread it over more CUs (32 single FP64
-  // runs of the argon sweep, 1e5 electrons each: 1.21e10 real/s with 128, 1.07e10 with 256).
-  swarm_launch_opts single{};
-  single.block_size = 128;
-  h->opts = resolve_opts(&single, params->precision);
+  // (Single runs of a swarm take the same default as batches.  Work-groups of 128 were better
+  // while draining waves waited for their last lane; since they do not, 256 with the trigger of
+  // the instance is: 1e5 electrons x 2000 argon collisions at 100 Td, FP64 13.4 -> 9.7 ms, FP32
+  // 6.0 -> 4.9 ms, at 1 Td 64.5 -> 62.9 and 28.7 -> 28.1 ms.)
+  h->opts = resolve_opts(nullptr, params->precision);
   return SWARM_OK;
 }
 
@@ -865,11 +865,14 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
       if ((e = launch_fill_u64(&d.ctr->parked, 0ull, 1, s)) != hipSuccess) return hip_fail(e, "park counter");
       const int64_t want = (n_parked + count + o.block_size - 1) / o.block_size;
       const TeamShape team = may_team ? team_shape(static_cast<double>(n_parked + count), d.trials) : TeamShape{};
+      // (the triggers of k_build_constants are for launches whose draining waves do not park)
+      constexpr int kRealTrigger = 32;
       const int grid = team.lanes > 1
           ? team_grid(team, (n_parked + count + team.per_group() - 1) / team.per_group())
           : static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want * 4, static_cast<int64_t>(dev.n_cu) * per_cu)));
       const int64_t park_min = hc.dropped != 0 || park_lanes == 0 ? 0 : std::max<int64_t>(1, lanes / 8);
-      if ((e = launch_swarm_real(h->d_desc, d.precision, h->has_b, trace, ext, o.block_size, grid, o.pending_trigger, lds,
+      if ((e = launch_swarm_real(h->d_desc, d.precision, h->has_b, trace, ext, o.block_size, grid,
+                                 o.pending_trigger ? o.pending_trigger : kRealTrigger, lds,
                                  ch_off, ll.cum_off, first, count, hc.dropped != 0 ? 1 : 0, park_in, n_parked, park_out,
                                  park_min, park_lanes, queued, s, team)) != hipSuccess)
         return hip_fail(e, "swarm kernel launch");

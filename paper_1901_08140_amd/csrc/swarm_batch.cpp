@@ -315,6 +315,7 @@ swarm_status swarm_autotune(swarm_t* handles, const swarm_job* jobs, int32_t n, 
   };
   swarm_launch_opts cur = resolve_opts(nullptr, handles[0] ? handles[0]->desc.precision : 0);
   cur.use_graph = 0;
+  cur.pending_trigger = 32;   // probed below; the options returned hold one number for all
   double t = 0.0;
   swarm_status st = time_it(cur, &t);   // warm-up
   if (st != SWARM_OK) return st;

@@ -176,6 +176,7 @@ struct InstanceDesc {
   // (the host sets it to the top node, the build lowers it), and the trials per real collision
   // there.  They shape launches only; no result depends on them.
   uint32_t balance_node;
+  int32_t trigger;            // waiting lanes of a full wave at which it serves them, by default
   double trials;
 };
 
@@ -207,7 +208,7 @@ hipError_t launch_build(InstanceDesc* d_desc, const InstanceDesc& h_desc, hipStr
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_mark_empty(swarm_record* r, int64_t n, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t* p, uint64_t v, int64_t n, hipStream_t s);
-// service_waves > 0 (and no trace): the pooled schedule, pool at LDS offset pool_off.  A team
+// pending_trigger 0: every instance's own.  service_waves > 0 (and no trace): the pooled schedule, pool at LDS offset pool_off.  A team
 // launch of one instance may leave d_items NULL: n_items ranges of team.per_group() electrons.
 hipError_t launch_swarm_dummy(const InstanceDesc* d_desc, const WorkItem* d_items, int32_t n_items,
                               int32_t* d_item_counter, int precision, bool has_b, bool trace,

@@ -333,7 +333,9 @@ __global__ void k_build_rates(InstanceDesc* desc) {
   const double w = kQe * d.B / kMe, cb = cos(d.B_angle), sb = sin(d.B_angle);
   const double heat = kQe * d.E * d.E / kMe *
                       (d.B > 0.0 ? cb * cb / acc + sb * sb * acc / (acc * acc + w * w) : 1.0 / acc);
-  if (loss >= heat) atomicMin(&desc->balance_node, static_cast<uint32_t>(g));
+  const uint64_t prevails = __ballot(loss >= heat);      // one atomic per wave: they queue on one address
+  if (prevails != 0 && static_cast<int>(__lane_id()) == __ffsll(static_cast<long long>(prevails)) - 1)
+    atomicMin(&desc->balance_node, static_cast<uint32_t>(g));
 }
 
 // Pairs (F[g], F[g+1]-F[g]) of every running sum (node major) and of the total rate.  The
@@ -434,6 +436,12 @@ __global__ void k_build_constants(InstanceDesc* desc) {
     // returns to the last collision after fails their runs behave like 4.
     d.trials = 1.0 + 1.5 * (nup / F[min(d.balance_node, static_cast<uint32_t>(d.G - 1))] - 1.0);
     if (d.trial_strategy != SWARM_TRIAL_CONSTANT) d.trials = fmin(d.trials, 4.0);
+    // The more trials a collision takes, the longer a wave waits for its next candidates and the
+    // sooner it should serve those it has.  Argon, 16 x 1e5 electrons, ms with 24, 28, 32, 40 and
+    // 48 waiting lanes: 1 Td (trials 8) FP32 271, 270, 282, 289, 325 and FP64 347, 352, 356, 391,
+    // 456; 3 Td (4.3) FP32 163, 161, 158, 159, 169 and FP64 198, 195, 194, 200, 219; 100 Td (3.1)
+    // FP32 83, 82, 79, 76, 78 and FP64 93, 91, 88, 84, 86; 1000 Td (1.7) the same for all.
+    d.trigger = d.trials >= 6.0 ? 26 : d.trials >= 3.8 ? 32 : 40;
     d.inv_majorant = 1.0 / nup;
     d.majorant_f = static_cast<float>(nup);
     d.cT_f = static_cast<float>(kLn2 / nup);
@@ -1830,7 +1838,7 @@ __global__ void __launch_bounds__(512) k_swarm_dummy(const InstanceDesc* __restr
       // real-collision candidate (or none can go on), then serve them together.  (`drawing`
       // is carried to the next pass, so the test is made once per pass.)
       bool drawing = L.state == ST_ACTIVE;
-      const int trig = wave_trigger(drawing, pend_trig);
+      const int trig = wave_trigger(drawing, pend_trig > 0 ? pend_trig : d.trigger);
       for (;;) {
         if (drawing) trial_block<R, HB, EXT>(L, C, s_nu);
         drawing = L.state == ST_ACTIVE;
