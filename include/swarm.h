@@ -342,7 +342,8 @@ typedef struct {
  * choice.  Zero fields mean "autotune" (swarm_autotune) or the built-in default. */
 typedef struct {
   int32_t block_size;      /* 64..1024, multiple of 64 */
-  int32_t chunk;           /* electrons per work item (multiple of block_size) */
+  int32_t chunk;           /* electrons a work-group's waves take at a time together
+                              (multiple of block_size) */
   int32_t pending_trigger; /* lanes waiting on a real collision before a full wave serves them
                               (1..64); 0: by the trials a collision of the instance takes */
   int32_t use_graph;       /* capture the launch in a hipGraph and replay it */

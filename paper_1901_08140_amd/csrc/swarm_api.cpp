@@ -340,68 +340,82 @@ hipError_t TallyPlan::launch(const InstanceDesc* d_descs, hipStream_t s) {
                         static_cast<double*>(d_tot.p), static_cast<swarm_tallies_t*>(d_out.p), s);
 }
 
-// Work items: instances with the largest collision budgets first (or the largest `rank`, the
-// expected device work per electron, where the caller measured it), so that the long items
-// start early and the persistent grid drains evenly.  An item holds up to `chunk` electrons;
-// when `slots` (resident work-groups) is given, an instance's items are cut smaller, down to
-// one electron per lane (`block`), so that no item holds much more than 1/slots of the
-// launch's work (electrons x collisions) and a small launch still spreads over the whole GPU.
-void make_items(const std::vector<int64_t>& n_e, const std::vector<int64_t>& n_c, int64_t chunk,
-                std::vector<WorkItem>& items, int64_t slots, int64_t block, const std::vector<double>* rank) {
-  items.clear();
-  std::vector<int> order(n_e.size());
-  for (size_t i = 0; i < order.size(); ++i) order[i] = static_cast<int>(i);
-  if (rank) std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return (*rank)[a] > (*rank)[b]; });
-  else std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return n_c[a] > n_c[b]; });
-  double total = 0.0;
-  for (size_t i = 0; i < n_e.size(); ++i) total += static_cast<double>(n_e[i]) * static_cast<double>(n_c[i]);
-  // Guided sizes: the last part of the work (about one item of two electrons per lane for
-  // every resident work-group) is cut into small items, so the launch ends on a fine tail,
-  // while the items before it keep `chunk` electrons (fewer item boundaries, at each of which
-  // a work-group waits for its slowest lane).  On the argon sweep (32 x 1e5 x 2e4, items of
-  // eight electrons per lane) this gave 835 ms per FP32 step against 893 ms without the
-  // small tail, and FP64 2413 ms against 2450 ms.
-  double n_all = 0.0;
-  for (size_t i = 0; i < n_e.size(); ++i) n_all += static_cast<double>(n_e[i]);
-  const int64_t small = block > 0 ? 2 * block : chunk;
-  const double tail = (slots > 0 && block > 0 && n_all > 0.0)
-                          ? std::min(0.5 * total, static_cast<double>(slots) * static_cast<double>(small) * total / n_all)
-                          : 0.0;
-  double left = total;
-  for (int i : order) {
-    int64_t ch = chunk;
-    if (slots > 0 && block > 0 && n_c[i] > 0) {
-      const double want = total / static_cast<double>(slots) / static_cast<double>(n_c[i]);
-      const int64_t w = (static_cast<int64_t>(std::min(want, 1e15)) + block - 1) / block * block;
-      ch = std::max(block, std::min(chunk, w));
-    }
-    for (int64_t f = 0; f < n_e[i];) {
-      const int64_t c = left <= tail ? std::min(ch, small) : ch;
-      WorkItem w;
-      w.inst = i;
-      w.pad = 0;
-      w.first = f;
-      w.count = std::min<int64_t>(c, n_e[i] - f);
-      items.push_back(w);
-      f += w.count;
-      left -= static_cast<double>(w.count) * static_cast<double>(n_c[i]);
-    }
-  }
+// Team steps per collision: a step tests 2 g trials, each a hit with probability 1/t.
+static double team_steps(double trials, int g) { return 1.0 / (1.0 - std::pow(1.0 - 1.0 / std::max(1.0, trials), 2.0 * g)); }
+
+// Work per electron: a collision pass counts as about three trials; a team makes a step of 2 g
+// trials at once, and its collision counts as about two and a half such steps.
+double electron_work(double n_collisions, double trials, int team_lanes) {
+  return n_collisions * (team_lanes <= 1 ? trials + 3.0 : team_steps(trials, team_lanes) + 2.5);
 }
 
-// Default launch shape (the autotuner's pick on MI355X for the argon-like sweep, probed with
-// a fifth of the collision budget): work-groups of 256, items of 4 electrons per lane in FP32
-// and 8 in FP64.  Against 128 lanes and 3 per lane the FP32 step went 833 -> 789 ms, and FP64
-// with 8 per lane 2409 -> 2131 ms (32 x 1e5 x 2e4).
-int default_block(int) { return 256; }
+// The launch lasts about T, its work over its work-groups.  An instance whose electrons take w
+// each can run floor(T / w) of them one after another in a lane, and starts with as many
+// work-groups as that needs (all of its electrons at once where w is near T or above).  The
+// longest electrons come first; instances that find no work-group left start when one is free.
+// A work-group keeps its instance, with no wait between electrons, until the instance's
+// electrons are all taken, and then helps where most work is left (next_instance).  Against
+// a share in proportion to the work alone (ms): 16 adaptive argon swarms of 50,000 electrons,
+// 2.4 a lane, 55.4 | 51.6, as it makes whole rounds; 40 uneven swarms of up to 10,000 electrons
+// 33.2 | 29.5, as the longest electrons all start first; 20 argon fields x 60,000 93 | 94.
+LaunchPlan plan_launch(const std::vector<int64_t>& n_e, const std::vector<double>& work, int64_t per_group, int64_t slots) {
+  LaunchPlan p;
+  const size_t n = n_e.size();
+  std::vector<int64_t> most(n), given(n, 0);
+  std::vector<int> order(n);
+  int64_t groups = 0;
+  double total = 0.0;
+  for (size_t i = 0; i < n; ++i) {
+    order[i] = static_cast<int>(i);
+    most[i] = (n_e[i] + per_group - 1) / per_group;
+    groups += most[i];
+    total += static_cast<double>(most[i]) * work[i];
+    p.weight.push_back(std::max(1e-30f, static_cast<float>(work[i])));
+  }
+  p.grid = static_cast<int>(std::max<int64_t>(1, std::min(groups, slots)));
+  const double T = 0.9 * total / p.grid;     // (a margin: the work is an estimate)
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
+  int64_t left = p.grid;
+  for (int i : order) {
+    const int64_t rounds = std::max<int64_t>(1, static_cast<int64_t>(std::min(T / work[i], 1e9)));
+    given[i] = std::min(left, (most[i] + rounds - 1) / rounds);
+    left -= given[i];
+  }
+  for (int i : order) {
+    const int64_t more = std::min(left, most[i] - given[i]);
+    given[i] += more;
+    left -= more;
+  }
+  for (int i : order) p.first.insert(p.first.end(), given[i], i);
+  return p;
+}
 
-swarm_launch_opts resolve_opts(const swarm_launch_opts* o, int precision) {
+hipError_t LaunchPlan::upload(void* base, hipStream_t s) const {
+  char* b = static_cast<char*>(base) + counter_words() * 8;
+  hipError_t e = hipMemcpyAsync(b, first.data(), first.size() * 4, hipMemcpyHostToDevice, s);
+  if (e != hipSuccess) return e;
+  return hipMemcpyAsync(b + first.size() * 4, weight.data(), weight.size() * 4, hipMemcpyHostToDevice, s);
+}
+hipError_t LaunchPlan::clear(void* base, hipStream_t s) const {
+  return launch_fill_u64(static_cast<uint64_t*>(base), 0ull, static_cast<int64_t>(counter_words()), s);
+}
+ClaimPlan LaunchPlan::view(void* base, int32_t chunk) const {
+  char* b = static_cast<char*>(base) + counter_words() * 8;
+  return {static_cast<unsigned long long*>(base), reinterpret_cast<const int32_t*>(b),
+          reinterpret_cast<const float*>(b + first.size() * 4), n_inst(), chunk};
+}
+int32_t wave_chunk(const swarm_launch_opts& o) { return std::max(1, o.chunk / (o.block_size / 64)); }
+
+// Default launch shape: work-groups of 256 (the autotuner's pick on MI355X for the argon-like
+// sweep; 833 -> 789 ms per FP32 step against 128 with work items of that time).
+int default_block() { return 256; }
+
+swarm_launch_opts resolve_opts(const swarm_launch_opts* o) {
   swarm_launch_opts r{};
-  r.block_size = (o && o->block_size) ? o->block_size : default_block(precision);
-  // electrons per lane and work item: FP32 4, FP64 8 (measured on the argon sweep, the
-  // 256-instance batch and serving: small items balance uneven work; the slower FP64 lanes
-  // lose more to the wait for the slowest lane at every item boundary)
-  r.chunk = (o && o->chunk) ? o->chunk : r.block_size * (precision == SWARM_FP64 ? 8 : 4);
+  r.block_size = (o && o->block_size) ? o->block_size : default_block();
+  // electrons the lanes of a work-group take at a time, one each: any number from a half to four
+  // gave the same time (argon sweep 311 ms x 8000 collisions, FP64 252 to 255 ms x 2000)
+  r.chunk = (o && o->chunk) ? o->chunk : r.block_size;
   r.use_graph = o ? o->use_graph : 0;
   r.block_size = std::max(64, std::min(1024, (r.block_size / 64) * 64));
   r.chunk = std::max(r.block_size, (r.chunk / r.block_size) * r.block_size);
@@ -417,10 +431,13 @@ bool free_shape(const swarm_launch_opts* o) {
   return !o || (o->block_size == 0 && o->chunk == 0 && o->pending_trigger == 0 && o->service_waves == 0);
 }
 
-// A team of g lanes tests 2 g trials of its electron at once, so with 2 g above the t trials
-// of a collision it makes about one step per collision; but it holds g lanes for it, so it
-// pays only while the electrons leave lanes of the device idle.  Measured against the one-lane
-// kernel at its best block and trigger (kernel ms, 800-1500 collisions; one lane | teams):
+// A team of g lanes makes about one step per collision once 2 g exceeds the trials t that a
+// collision takes, but it holds g lanes for it.  The launch is taken to last as long as its
+// work at full occupancy plus its longest chain of collisions on a wave with a SIMD to itself;
+// with the constants below (FP32, microseconds and lane instructions per collision, fitted to
+// argon at 1 to 900 Td) that gives the runs of the table within 10 to 20%, and the g of the
+// shortest one is taken.  Kernel ms, 800-1500 collisions, one lane at its best block and
+// trigger | teams (g):
 //   electrons                     25         1000         1e4         2e4        4e4        1e5
 //   93:7 Ar:CO2 2.4 Td FP64   15.8|3.4(16) 19.5|3.5(16) 20.6|7.4(16) 22.2|10.2(8) 21.6|14.7(8) 29.3|30.2(2)
 //   Ar:CO2 8 Td 0.5 T FP32     4.4|1.7(16)  5.7|1.7(16)  5.6|2.6(8)   6.0|3.1(8)   6.1|4.2(8)   7.1|7.7(2)
@@ -430,39 +447,49 @@ bool free_shape(const swarm_launch_opts* o) {
 //   argon 100 Td FP32          2.4|1.9(8)   2.7|1.9(8)   2.6|2.1(4)   2.8|2.4(4)   3.0|3.1(4)   3.9|4.7(2)
 //   argon 900 Td FP32          1.9|1.8(4)   2.0|1.8(4)   2.0|2.0(4)   2.2|2.2(2)   2.4|2.6(2)   3.2|4.0(2)
 //   Maxwell gas FP32           1.1|1.4(2)   1.1|1.4(2)   1.2|1.5(2)                1.6|1.9(2)   2.3|2.7(2)
-// The lanes that may be given out are read off these runs: they grow with t, and a team with
-// most of its trials beyond the hit (2 g > 4.5 t) gets fewer.  Few electrons whose collisions
-// take many steps are spread over all SIMDs, fewer teams in a wave, so that a team waits less
-// for the others (argon 1 Td, 1000 electrons: 2.6 against 3.3 ms); otherwise full waves are as
-// fast.
-TeamShape team_shape(double wide, double trials) {
-  TeamShape s;
-  if (!(trials >= 1.2)) return s;
+// Few electrons whose collisions take many steps are spread over all SIMDs, fewer teams in a
+// wave, so that a team waits less for the others (argon 1 Td, 1000 electrons: 2.6 against
+// 3.3 ms); otherwise full waves are as fast.
+TeamShape team_shape(const std::vector<int64_t>& n_e, const std::vector<double>& n_c, const std::vector<double>& trials) {
   const double simds = 4.0 * device_info().n_cu;
-  const double lanes = simds * std::min(300.0, std::max(40.0, 5.0 * trials * trials));
-  int g = 1;
-  while (g < 16 && g < 2.25 * trials) g *= 2;
-  while (g > 1 && wide * g > (2.0 * g > 4.5 * trials ? 0.6 : 1.0) * lanes) g /= 2;
-  if (g == 1) return s;
-  s.lanes = g;
-  const int full = 64 / g;
-  s.per_wave = trials < 6.0 ? full
-                            : static_cast<int>(std::min<double>(full, std::max(1.0, std::ceil(wide / simds))));
+  const double slots_per_us = simds * 64 * 600.0;        // lane instructions, 2.4 GHz / 4
+  TeamShape s;
+  double best = 0.0, wide = 0.0, mean_t = 0.0, total_c = 0.0;
+  for (size_t i = 0; i < n_e.size(); ++i) {
+    const double c = static_cast<double>(n_e[i]) * n_c[i];
+    mean_t += c * trials[i];
+    total_c += c;
+  }
+  mean_t /= std::max(1.0, total_c);
+  for (int g = 1; g <= 16; g *= 2) {
+    double slots = 0.0, chain = 0.0, sum = 0.0;
+    for (size_t i = 0; i < n_e.size(); ++i) {
+      const double n = static_cast<double>(n_e[i]);
+      double lanes, us;
+      if (g == 1) {
+        lanes = 100.0 * trials[i] + 60.0;
+        us = 0.38 * trials[i] + 0.55;
+      } else {
+        const double steps = team_steps(trials[i], g);
+        lanes = 260.0 * g * steps;
+        us = 0.85 * steps + 0.35;
+      }
+      slots += n * n_c[i] * lanes;
+      sum += n * n_c[i] * us;
+      chain = std::max(chain, n_c[i] * us);
+    }
+    const double t = slots / slots_per_us + chain;
+    if (g == 1 || t < best) {
+      best = t;
+      s.lanes = g;
+      wide = chain > 0.0 ? sum / chain : 0.0;      // electrons that run at once, on average
+    }
+  }
+  if (s.lanes == 1) return s;
+  const int full = 64 / s.lanes;
+  s.per_wave = mean_t < 6.0 ? full : static_cast<int>(std::min<double>(full, std::max(1.0, std::ceil(wide / simds))));
   s.block = wide <= simds * s.per_wave ? 64 : 256;
   return s;
-}
-
-// Several instances: the electrons that run at once on average, the launch's work over that
-// of its longest electron.
-TeamShape team_shape(const std::vector<int64_t>& n_e, const std::vector<int64_t>& work, const std::vector<double>& trials) {
-  double total = 0.0, longest = 0.0, t = 0.0;
-  for (size_t i = 0; i < n_e.size(); ++i) {
-    const double w = static_cast<double>(work[i]) * trials[i];
-    total += static_cast<double>(n_e[i]) * w;
-    t += static_cast<double>(n_e[i]) * w * trials[i];
-    longest = std::max(longest, w);
-  }
-  return total > 0.0 ? team_shape(total / longest, t / total) : TeamShape{};
 }
 
 }  // namespace swarm_impl
@@ -614,7 +641,7 @@ static swarm_status build_swarm(swarm* h, const swarm_component* comps, int32_t 
   // while draining waves waited for their last lane; since they do not, 256 with the trigger of
   // the instance is: 1e5 electrons x 2000 argon collisions at 100 Td, FP64 13.4 -> 9.7 ms, FP32
   // 6.0 -> 4.9 ms, at 1 Td 64.5 -> 62.9 and 28.7 -> 28.1 ms.)
-  h->opts = resolve_opts(nullptr, params->precision);
+  h->opts = resolve_opts(nullptr);
   return SWARM_OK;
 }
 
@@ -694,8 +721,6 @@ swarm_status swarm_arena_bytes(const swarm_component* comps, int32_t n_comps, co
   if (real && capacity > n_electrons) run += blk(static_cast<size_t>(capacity - n_electrons) * sizeof(ChildState));
   // real mode: the two buffers of parked electrons, for the most lanes a device can hold
   if (real) run += blk(2 * static_cast<size_t>(parked_capacity(static_cast<int64_t>(device_info().n_cu) * 2048, 64)) * sizeof(ParkedState));
-  // dummy-mode work items: at most one per 64 electrons (the smallest work-group), plus the counter
-  if (!real) run += blk(static_cast<size_t>((n_electrons + 63) / 64) * sizeof(WorkItem) + 256);
   *bytes = static_cast<int64_t>(blk(tables) + run);
   return SWARM_OK;
 }
@@ -733,7 +758,7 @@ swarm_status swarm_set_trace(swarm_t h, const uint64_t* ids, int32_t n_ids, int3
 swarm_status swarm_set_launch_opts(swarm_t h, const swarm_launch_opts* opts) {
   if (!h) return fail(SWARM_ERR_INVALID_ARG, "NULL handle");
   if (h->in_flight) return busy();
-  h->opts = resolve_opts(opts, h->desc.precision);
+  h->opts = resolve_opts(opts);
   h->free_shape = free_shape(opts);
   return SWARM_OK;
 }
@@ -812,28 +837,14 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
   };
   if ((e = hipEventRecord(h->ev[0], s)) != hipSuccess) return hip_fail(e, "event");
   if (!real) {
-    // enough work items to give every resident work-group several of them
-    const int64_t slots = static_cast<int64_t>(dev.n_cu) * per_cu;
-    int64_t chunk = (n_electrons + 4 * slots - 1) / (4 * slots);
-    chunk = ((chunk + o.block_size - 1) / o.block_size) * o.block_size;
-    chunk = std::max<int64_t>(o.block_size, std::min<int64_t>(chunk, o.chunk));
-    const TeamShape team = may_team ? team_shape(static_cast<double>(n_electrons), d.trials) : TeamShape{};
-    std::vector<WorkItem> items;   // a team launch takes its ranges from their number alone
-    if (team.lanes == 1) make_items({n_electrons}, {n_collisions}, chunk, items, 0, 0);
-    const int64_t n_items = team.lanes > 1 ? (n_electrons + team.per_group() - 1) / team.per_group()
-                                           : static_cast<int64_t>(items.size());
-    if ((e = h->items.ensure(items.size() * sizeof(WorkItem) + 256)) != hipSuccess) return hip_fail(e, "work items");
-    h->h_items = items;
-    int32_t* d_ctr = reinterpret_cast<int32_t*>(static_cast<char*>(h->items.p) + items.size() * sizeof(WorkItem));
-    if (!items.empty() &&
-        (e = hipMemcpyAsync(h->items.p, h->h_items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s)) != hipSuccess)
-      return hip_fail(e, "work items");
-    if ((e = launch_fill_u32(reinterpret_cast<uint32_t*>(d_ctr), 0u, 1, s)) != hipSuccess) return hip_fail(e, "item counter");
-    const int grid = team.lanes > 1 ? team_grid(team, n_items)
-                                    : std::max(1, std::min<int>(static_cast<int>(n_items), dev.n_cu * per_cu));
-    if ((e = launch_swarm_dummy(h->d_desc, items.empty() ? nullptr : static_cast<const WorkItem*>(h->items.p),
-                                static_cast<int32_t>(n_items), d_ctr, d.precision, h->has_b, trace, ext, svc, o.block_size, grid,
-                                o.pending_trigger, lds, ch_off, ll.pool_off, ll.cum_off, s, team)) != hipSuccess)
+    const TeamShape team = may_team ? team_shape({n_electrons}, {static_cast<double>(n_collisions)}, {d.trials}) : TeamShape{};
+    const int64_t per_group = team.lanes > 1 ? team.per_group() : o.block_size;
+    const int64_t groups = (n_electrons + per_group - 1) / per_group;
+    const int grid = team.lanes > 1 ? team_grid(team, groups)
+                                    : static_cast<int>(std::min<int64_t>(groups, static_cast<int64_t>(dev.n_cu) * per_cu));
+    const ClaimPlan plan = {reinterpret_cast<unsigned long long*>(&d.ctr->gen_next), nullptr, nullptr, 1, wave_chunk(o)};
+    if ((e = launch_swarm_dummy(h->d_desc, plan, d.precision, h->has_b, trace, ext, svc, o.block_size, grid, o.pending_trigger,
+                                lds, ch_off, ll.pool_off, ll.cum_off, s, team)) != hipSuccess)
       return hip_fail(e, "swarm kernel launch");
     h->n_launches = 1;
     h->n_parked = 0;
@@ -864,7 +875,7 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
       if ((e = launch_fill_u64(&d.ctr->gen_next, 0ull, 1, s)) != hipSuccess) return hip_fail(e, "generation counter");
       if ((e = launch_fill_u64(&d.ctr->parked, 0ull, 1, s)) != hipSuccess) return hip_fail(e, "park counter");
       const int64_t want = (n_parked + count + o.block_size - 1) / o.block_size;
-      const TeamShape team = may_team ? team_shape(static_cast<double>(n_parked + count), d.trials) : TeamShape{};
+      const TeamShape team = may_team ? team_shape({n_parked + count}, {static_cast<double>(n_collisions)}, {d.trials}) : TeamShape{};
       // (the triggers of k_build_constants are for launches whose draining waves do not park)
       constexpr int kRealTrigger = 32;
       const int grid = team.lanes > 1

@@ -80,20 +80,31 @@ struct LdsLayout {
   int cum_off;     // running sums staged at this offset, or -1 (read from global memory)
 };
 LdsLayout lds_layout(int precision, int G, int nc, int service_waves, int table_layout);
-// Work items of `chunk` electrons (fewer towards the end of the launch), instance by instance:
-// the heaviest collision budget first, or the largest `rank` first where one is given (the
-// expected device work per electron); instances of equal rank in the caller's order.
-void make_items(const std::vector<int64_t>& n_e, const std::vector<int64_t>& n_c, int64_t chunk,
-                std::vector<WorkItem>& items, int64_t slots, int64_t block,
-                const std::vector<double>* rank = nullptr);
-swarm_launch_opts resolve_opts(const swarm_launch_opts* o, int precision);
+// The work-groups of a launch over several instances: how many (at most `slots` resident ones,
+// per_group electrons at once in each) and which instance each starts with, given the expected
+// work per electron.  Held in device memory behind the counters of the electrons taken.
+struct LaunchPlan {
+  int grid = 1;
+  std::vector<int32_t> first;       // grid entries
+  std::vector<float> weight;        // per instance
+  int32_t n_inst() const { return static_cast<int32_t>(weight.size()); }
+  size_t counter_words() const { return weight.size() * kClaimStride; }
+  size_t bytes() const { return counter_words() * 8 + first.size() * 4 + weight.size() * 4; }
+  // Copies the lists behind the counters of `base` (bytes() long); the plan has to outlive the copy.
+  hipError_t upload(void* base, hipStream_t s) const;
+  hipError_t clear(void* base, hipStream_t s) const;        // no electron taken
+  ClaimPlan view(void* base, int32_t chunk) const;
+};
+// Expected device work of an electron, for comparison between the instances of a launch.
+double electron_work(double n_collisions, double trials, int team_lanes);
+LaunchPlan plan_launch(const std::vector<int64_t>& n_e, const std::vector<double>& work, int64_t per_group, int64_t slots);
+// Electrons a wave takes at a time: the option's share of a work-group's.
+int32_t wave_chunk(const swarm_launch_opts& o);
+swarm_launch_opts resolve_opts(const swarm_launch_opts* o);
 // Whether the caller left the launch shape to the library.
 bool free_shape(const swarm_launch_opts* o);
-// Team shape of a launch whose electrons keep about `wide` of them running at once, at
-// `trials` trials per real collision.
-TeamShape team_shape(double wide, double trials);
-// The same for a launch of several instances (electrons, expected work per electron, trials).
-TeamShape team_shape(const std::vector<int64_t>& n_e, const std::vector<int64_t>& work, const std::vector<double>& trials);
+// Team shape of a launch (electrons, collisions and trials per collision of every instance).
+TeamShape team_shape(const std::vector<int64_t>& n_e, const std::vector<double>& n_c, const std::vector<double>& trials);
 // Builds a swarm handle (validation, tables); with `mem` every device allocation of the
 // handle comes from that caller-owned region.
 swarm_status create_swarm(const swarm_component* comps, int32_t n_comps, const swarm_params* params,
@@ -115,9 +126,8 @@ struct swarm {
   swarm_impl::InstanceDesc desc{};          // host copy (device constants read back after build)
   swarm_impl::InstanceDesc* d_desc = nullptr;
   swarm_impl::DevBuf arena;                 // raw inputs, tables, descriptor, counters
-  swarm_impl::DevBuf records, children, items;
+  swarm_impl::DevBuf records, children;
   swarm_impl::DevBuf parked;                 // real mode: electrons parked between launches (two buffers)
-  std::vector<swarm_impl::WorkItem> h_items;
   swarm_impl::DevBuf trace_ids, trace_out, trace_count;
   int32_t n_trace = 0, max_events = 0;
   bool traced = false;
@@ -142,7 +152,7 @@ struct swarm {
 
   void bind_arena(swarm_impl::Arena* a) {
     mem = a;
-    for (swarm_impl::DevBuf* b : {&arena, &records, &children, &items, &parked, &trace_ids, &trace_out, &trace_count})
+    for (swarm_impl::DevBuf* b : {&arena, &records, &children, &parked, &trace_ids, &trace_out, &trace_count})
       b->arena = a;
     tally.bind(a);
   }

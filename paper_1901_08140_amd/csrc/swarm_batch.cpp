@@ -20,13 +20,12 @@ struct swarm_batch {
   int extended = 0;   // kernel level: 1 some instance uses an adaptive trial frequency,
                       // 2 some instance has moving targets or the relativistic mover
   hipStream_t stream = nullptr;
-  DevBuf descs, items;
+  DevBuf descs, plan_mem;
   std::vector<InstanceDesc> h_descs;
-  std::vector<WorkItem> h_items;
+  LaunchPlan plan;
   TallyPlan tally;
   swarm_launch_opts opts{};
   TeamShape team;                // of the launch, where the caller left its shape free
-  int grid = 1;
   size_t lds = 0;
   int ch_off = 0, pool_off = 0, cum_off = -1;
   hipGraph_t graph = nullptr;
@@ -37,7 +36,7 @@ struct swarm_batch {
   double device_ms = 0.0;
   std::vector<int64_t> ne, nc;   // electrons and collision budget per instance
   int64_t slots = 0;             // resident work-groups of the launch shape
-  bool reordered = false;        // items ordered by the measured work (after the first launch)
+  bool reordered = false;        // planned by the measured work (after the first launch)
 
   ~swarm_batch() {
     if (stream) (void)hipStreamSynchronize(stream);
@@ -51,19 +50,15 @@ struct swarm_batch {
 
 namespace {
 
-int32_t* item_counter(swarm_batch* b) {
-  return reinterpret_cast<int32_t*>(static_cast<char*>(b->items.p) + b->h_items.size() * sizeof(WorkItem));
-}
-
-// The device work of one batch launch: reset the work counter, run the persistent swarm
-// kernel over all work items, reduce the tallies of every instance.
+// The device work of one batch launch: clear the counters of the electrons taken, run the
+// persistent swarm kernel over all instances, reduce the tallies of every instance.
 hipError_t enqueue(swarm_batch* b) {
   hipError_t e;
-  if ((e = launch_fill_u32(reinterpret_cast<uint32_t*>(item_counter(b)), 0u, 1, b->stream)) != hipSuccess) return e;
-  if ((e = launch_swarm_dummy(static_cast<const InstanceDesc*>(b->descs.p), static_cast<const WorkItem*>(b->items.p),
-                              static_cast<int32_t>(b->h_items.size()), item_counter(b), b->precision, b->magnetic,
-                              false, b->extended, b->opts.service_waves, b->opts.block_size, b->grid,
-                              b->opts.pending_trigger, b->lds, b->ch_off, b->pool_off, b->cum_off, b->stream, b->team)) != hipSuccess)
+  if ((e = b->plan.clear(b->plan_mem.p, b->stream)) != hipSuccess) return e;
+  if ((e = launch_swarm_dummy(static_cast<const InstanceDesc*>(b->descs.p), b->plan.view(b->plan_mem.p, wave_chunk(b->opts)),
+                              b->precision, b->magnetic, false, b->extended, b->opts.service_waves, b->opts.block_size,
+                              b->plan.grid, b->opts.pending_trigger, b->lds, b->ch_off, b->pool_off, b->cum_off, b->stream,
+                              b->team)) != hipSuccess)
     return e;
   return b->tally.launch(static_cast<const InstanceDesc*>(b->descs.p), b->stream);
 }
@@ -83,44 +78,24 @@ hipError_t capture(swarm_batch* b) {
   return hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
 }
 
-// Electrons of a work item at most, and its unit: one electron per lane, or per team.
-int64_t item_unit(const swarm_batch* b) { return b->team.lanes > 1 ? b->team.per_group() : b->opts.block_size; }
-int64_t item_size(const swarm_batch* b) { return b->team.lanes > 1 ? b->team.per_group() : b->opts.chunk; }
-
-// Upload the work items and size the grid to them.
-hipError_t upload_items(swarm_batch* b, int per_cu) {
-  hipError_t e = b->items.ensure(b->h_items.size() * sizeof(WorkItem) + 256);
-  if (e != hipSuccess) return e;
-  if ((e = hipMemcpyAsync(b->items.p, b->h_items.data(), b->h_items.size() * sizeof(WorkItem), hipMemcpyHostToDevice,
-                          b->stream)) != hipSuccess)
-    return e;
-  b->grid = std::max(1, std::min<int>(static_cast<int>(b->h_items.size()), device_info().n_cu * per_cu));
-  return hipSuccess;
+// Plans the launch for the given work per electron and uploads the plan.
+hipError_t plan_batch(swarm_batch* b, const std::vector<double>& work) {
+  const int64_t per_group = b->team.lanes > 1 ? b->team.per_group() : b->opts.block_size;
+  b->plan = plan_launch(b->ne, work, per_group, b->slots);
+  hipError_t e = b->plan_mem.ensure(b->plan.bytes());
+  return e == hipSuccess ? b->plan.upload(b->plan_mem.p, b->stream) : e;
 }
 
-// After the first launch, the items are ordered by each instance's measured device work per
-// electron, collision budget x (trials per real collision + 3, the collision pass counted as
-// about three trials), longest first.  The order matters as much as the item size (the argon
-// sweep listed with its fast instances first took 1071 ms instead of 873 ms), and the caller's
-// order need not be the right one.  Item sizes stay those of the collision budgets (items
-// sized by the measured cost made the step slower).  Results do not depend on the order.
+// After the first launch the plan takes each instance's measured trials per real collision
+// instead of the expected ones.  Results do not depend on the plan.
 hipError_t reorder(swarm_batch* b) {
-  std::vector<double> rank(b->hs.size());
-  for (size_t i = 0; i < rank.size(); ++i) {
+  std::vector<double> work(b->hs.size());
+  for (size_t i = 0; i < work.size(); ++i) {
     const double reals = static_cast<double>(b->h_out[i].n_real);
     const double trials = reals + static_cast<double>(b->h_out[i].n_null) + static_cast<double>(b->h_out[i].n_forbidden);
-    rank[i] = static_cast<double>(b->nc[i]) * (reals > 0 ? trials / reals + 3.0 : 4.0);
+    work[i] = electron_work(static_cast<double>(b->nc[i]), reals > 0 ? trials / reals : 1.0, b->team.lanes);
   }
-  std::vector<WorkItem> items;
-  make_items(b->ne, b->nc, item_size(b), items, b->slots, item_unit(b), &rank);
-  const bool same = items.size() == b->h_items.size() &&
-                    std::equal(items.begin(), items.end(), b->h_items.begin(), [](const WorkItem& x, const WorkItem& y) {
-                      return x.inst == y.inst && x.first == y.first && x.count == y.count;
-                    });
-  if (same) return hipSuccess;
-  b->h_items.swap(items);
-  const int per_cu = static_cast<int>(b->slots / std::max(1, device_info().n_cu));
-  hipError_t e = upload_items(b, per_cu);
+  hipError_t e = plan_batch(b, work);
   if (e == hipSuccess && b->exec) e = capture(b);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   return e;
@@ -157,7 +132,7 @@ swarm_status swarm_batch_create(swarm_t* handles, const swarm_job* jobs, int32_t
     b->hs.push_back(h);
     b->jobs.push_back(jobs[i]);
   }
-  b->opts = resolve_opts(opts, b->precision);
+  b->opts = resolve_opts(opts);
   hipError_t e = hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking);
   if (e != hipSuccess) return hip_fail(e, "hipStreamCreate");
   if ((e = hipEventCreate(&b->ev0)) != hipSuccess || (e = hipEventCreate(&b->ev1)) != hipSuccess)
@@ -194,11 +169,13 @@ swarm_status swarm_batch_create(swarm_t* handles, const swarm_job* jobs, int32_t
   b->ch_off = ll.ch_off;
   b->pool_off = ll.pool_off;
   b->cum_off = ll.cum_off;
-  if (free_shape(opts)) {
-    std::vector<double> trials;
-    for (const swarm* h : b->hs) trials.push_back(h->desc.trials);
-    b->team = team_shape(ne, nc, trials);
+  std::vector<double> trials, budget, work;
+  for (int i = 0; i < n; ++i) {
+    trials.push_back(b->hs[i]->desc.trials);
+    budget.push_back(static_cast<double>(nc[i]));
   }
+  if (free_shape(opts)) b->team = team_shape(ne, budget, trials);
+  for (int i = 0; i < n; ++i) work.push_back(electron_work(budget[i], trials[i], b->team.lanes));
   const int per_cu = b->team.lanes > 1
       ? swarm_kernel_max_blocks_per_cu(b->precision, b->magnetic, false, false, b->extended, 0, b->team.block, b->lds, true)
       : swarm_kernel_max_blocks_per_cu(b->precision, b->magnetic, false, false, b->extended, b->opts.service_waves,
@@ -206,10 +183,9 @@ swarm_status swarm_batch_create(swarm_t* handles, const swarm_job* jobs, int32_t
   b->slots = static_cast<int64_t>(device_info().n_cu) * per_cu;
   b->ne = ne;
   b->nc = nc;
-  make_items(ne, nc, item_size(b.get()), b->h_items, b->slots, item_unit(b.get()));
   if ((e = b->descs.ensure(n * sizeof(InstanceDesc))) != hipSuccess) return hip_fail(e, "descriptors");
   if ((e = hipMemcpyAsync(b->descs.p, b->h_descs.data(), n * sizeof(InstanceDesc), hipMemcpyHostToDevice, b->stream)) != hipSuccess ||
-      (e = upload_items(b.get(), per_cu)) != hipSuccess)
+      (e = plan_batch(b.get(), work)) != hipSuccess)
     return hip_fail(e, "uploading batch");
   if ((e = b->tally.prepare(ne, b->stream)) != hipSuccess) return hip_fail(e, "tally plan");
   if ((e = hipStreamSynchronize(b->stream)) != hipSuccess) return hip_fail(e, "uploading batch");
@@ -313,7 +289,7 @@ swarm_status swarm_autotune(swarm_t* handles, const swarm_job* jobs, int32_t n, 
     swarm_batch_destroy(b);
     return st;
   };
-  swarm_launch_opts cur = resolve_opts(nullptr, handles[0] ? handles[0]->desc.precision : 0);
+  swarm_launch_opts cur = resolve_opts(nullptr);
   cur.use_graph = 0;
   cur.pending_trigger = 32;   // probed below; the options returned hold one number for all
   double t = 0.0;

@@ -88,7 +88,7 @@ struct ChildState {
 // concurrently sit on 128-byte lines of their own, so their atomics do not queue behind
 // each other.
 struct RunCounters {
-  uint64_t gen_next;      // real mode: electrons of the running generation taken so far
+  uint64_t gen_next;      // electrons taken so far, of the run (real mode: of the running generation)
   uint64_t pad0[15];
   uint64_t child_tail;    // real mode: reserved secondary slots
   uint64_t pad1[15];
@@ -180,11 +180,19 @@ struct InstanceDesc {
   double trials;
 };
 
-struct WorkItem {
-  int32_t inst;
-  int32_t pad;
-  int64_t first;       // first electron index of the item
-  int64_t count;       // electrons in the item
+// How a launch hands out the electrons of its instances.  Every instance has a counter of
+// those taken (64 bytes apart); a wave takes some at a time and passes them to its lanes.
+// A work-group starts with instance first[blockIdx.x] (NULL: instance 0), stays with it until
+// all of its electrons are taken and run, and goes on with the instance that has the most work
+// left, weight (expected work per electron) times electrons not taken.
+constexpr int kClaimStride = 8;           // counters are this many 64-bit words apart
+struct ClaimPlan {
+  unsigned long long* taken;
+  const int32_t* first;
+  const float* weight;
+  int32_t n_inst;
+  int32_t chunk;                          // electrons a wave takes at a time while many are left
+  uint32_t scarce = 0;                    // from this many on: no more than its idle lanes need
 };
 
 struct TallyTile {
@@ -208,10 +216,8 @@ hipError_t launch_build(InstanceDesc* d_desc, const InstanceDesc& h_desc, hipStr
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_mark_empty(swarm_record* r, int64_t n, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t* p, uint64_t v, int64_t n, hipStream_t s);
-// pending_trigger 0: every instance's own.  service_waves > 0 (and no trace): the pooled schedule, pool at LDS offset pool_off.  A team
-// launch of one instance may leave d_items NULL: n_items ranges of team.per_group() electrons.
-hipError_t launch_swarm_dummy(const InstanceDesc* d_desc, const WorkItem* d_items, int32_t n_items,
-                              int32_t* d_item_counter, int precision, bool has_b, bool trace,
+// pending_trigger 0: every instance's own.  service_waves > 0 (and no trace): the pooled schedule, pool at LDS offset pool_off.
+hipError_t launch_swarm_dummy(const InstanceDesc* d_desc, ClaimPlan plan, int precision, bool has_b, bool trace,
                               int ext, int service_waves, int block_size, int grid, int pending_trigger,
                               size_t lds_bytes, int ch_off, int pool_off, int cum_off, hipStream_t s,
                               TeamShape team);

@@ -687,7 +687,7 @@ struct Lane {
   R e_q0, e_vz, e_vpar, e_Bc, e_Bs;  // the same in energy units (FP32 scaled by m/2e)
   double se, sep;           // sums of energies before / after real collisions
   uint64_t id;
-  int64_t rec;              // record slot
+  int64_t rec;              // real mode: record slot (a primary's is its id)
   uint32_t block, k, k_start, k_stop, G, D, nforb, nover, flags;
   uint32_t nfirst;          // blocks whose first trial was not null (real or forbidden)
   int state;
@@ -1143,7 +1143,7 @@ __device__ __forceinline__ void init_primary(Lane<R>& L, const Consts<R>& C,
 }
 
 template <typename R>
-__device__ __forceinline__ void write_record(const InstanceDesc& d, const Lane<R>& L) {
+__device__ __forceinline__ void write_record(const InstanceDesc& d, const Lane<R>& L, int64_t slot) {
   swarm_record r;
   r.id = L.id;
   r.flags = L.flags & ~kRetryFlag;
@@ -1162,7 +1162,7 @@ __device__ __forceinline__ void write_record(const InstanceDesc& d, const Lane<R
   r.t = L.t;
   r.sum_eps = L.se;
   r.sum_epsp = L.sep;
-  d.records[L.rec] = r;
+  d.records[slot] = r;
 }
 
 // Resumable state of a lane at a real-collision boundary (the anchor, T = 0): written at the
@@ -1756,50 +1756,128 @@ __device__ __forceinline__ int wave_trigger(bool drawing, int pend_trig) {
   return (static_cast<int>(__popcll(__ballot(drawing))) * pend_trig + 63) >> 6;
 }
 
+// A value the whole wave holds, kept in scalar registers.
+__device__ __forceinline__ int64_t wave_uniform(int64_t x) {
+  const uint64_t u = static_cast<uint64_t>(x);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
+  return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// The electrons a wave has taken and not yet given to a lane, [next, end), and whether none
+// are left to take.  While many are left a wave takes `chunk` at a time, so that lanes rarely
+// wait on the device-wide counter; towards the end (left <= scarce) it takes only what its idle
+// lanes need, so that no wave holds electrons that another could run.  (32 bits: the records of
+// 2^32 electrons would not fit the device.)
+struct WaveClaim {
+  uint32_t next = 0, end = 0;
+  bool none = false;
+};
+
+// Electrons for the wave's idle lanes (with teams for the first lane of each, `firsts`): true,
+// with the electron's index in *e, for a lane that got one.
+__device__ __forceinline__ bool claim_electron(WaveClaim& w, bool is_idle, uint64_t idle, uint64_t firsts, int sub,
+                                               unsigned long long* taken, uint32_t count, uint32_t chunk, uint32_t scarce,
+                                               uint32_t* e) {
+  const uint64_t asking = idle & firsts;
+  const uint32_t wanted = static_cast<uint32_t>(__popcll(asking));
+  if (w.next >= w.end && !w.none) {
+    const int leader = __ffsll(static_cast<long long>(idle)) - 1;
+    const uint32_t n = count - w.end > scarce ? chunk : wanted;
+    unsigned long long base = 0;
+    if (static_cast<int>(__lane_id()) == leader) base = atomicAdd(taken, static_cast<unsigned long long>(n));
+    const uint32_t got = __builtin_amdgcn_readfirstlane(
+        static_cast<uint32_t>(__shfl(base < count ? static_cast<uint32_t>(base) : count, leader)));
+    w.next = got;
+    w.end = got + min(n, count - got);
+    w.none = got >= count;
+  }
+  // rank of the lane's electron among those asked for (the team's first lane counts once)
+  const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(asking >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(asking), 0u)) -
+                        (sub != 0 ? 1u : 0u);
+  const uint32_t avail = w.end - w.next;
+  *e = w.next + rank;
+  w.next += __builtin_amdgcn_readfirstlane(min(avail, wanted));
+  return is_idle && rank < avail;
+}
+
+// Staging of an instance's tables in LDS: the padded total-rate pairs, the channel
+// descriptors, the logarithm table (FP64) and with table layout 1 the running sums.
+template <typename R>
+__device__ __forceinline__ void stage_instance(const InstanceDesc& d, unsigned char* smem, ChannelDev* s_ch,
+                                               double* s_logtab, int cum_off) {
+  using PT = typename Pair<R>::T;
+  PT* s_nu = reinterpret_cast<PT*>(smem);
+  const PT* src = reinterpret_cast<const PT*>(sizeof(R) == 8 ? static_cast<const void*>(d.nu64)
+                                                             : static_cast<const void*>(d.nu32));
+  for (int g = threadIdx.x; g <= d.G; g += blockDim.x) {
+    PT q = src[g > 0 ? g - 1 : 0];
+    if (g == 0) q.y = 0;
+    s_nu[g] = q;
+  }
+  for (int c = threadIdx.x; c < d.nc; c += blockDim.x) s_ch[c] = d.chan[c];
+  if constexpr (sizeof(R) == 8)
+    for (int j = threadIdx.x; j < kUnitLogStride * kUnitLogEntries; j += blockDim.x) s_logtab[j] = d.logtab[j];
+  stage_cum<R>(d, smem, cum_off);
+}
+
+// The instance a work-group goes on with: the one with the most work not taken, or -1.
+__device__ __forceinline__ int next_instance(const InstanceDesc* __restrict__ descs, const ClaimPlan& plan,
+                                             unsigned long long* s_best) {
+  if (plan.n_inst == 1) return -1;
+  __syncthreads();
+  if (threadIdx.x == 0) *s_best = 0ull;
+  __syncthreads();
+  for (int i = threadIdx.x; i < plan.n_inst; i += blockDim.x) {
+    const int64_t left = descs[i].n_electrons -
+        static_cast<int64_t>(__hip_atomic_load(&plan.taken[static_cast<int64_t>(i) * kClaimStride], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT));
+    if (left > 0) {
+      const uint32_t key = __float_as_uint(static_cast<float>(left) * plan.weight[i]);    // positive: ordered as bits
+      atomicMax(s_best, (static_cast<unsigned long long>(key) << 32) | static_cast<uint32_t>(0x7fffffff - i));
+    }
+  }
+  __syncthreads();
+  const unsigned long long best = *s_best;
+  return best == 0ull ? -1 : __builtin_amdgcn_readfirstlane(0x7fffffff - static_cast<int>(static_cast<uint32_t>(best)));
+}
+
+// Waves per SIMD the registers of the dummy kernel have to allow (asked for where the compiler
+// would end one or a few registers above the limit): FP32 5 (96 VGPRs), B with an adaptive trial
+// frequency 4 (128).
+template <typename R, bool HB, bool TR, int EXT>
+constexpr int dummy_waves() {
+  if (TR || sizeof(R) == 8 || EXT == 2) return 1;
+  return HB && EXT == 1 ? 4 : 5;
+}
+
 // ---------------------------------------------------------------------------------------
-// Dummy-mode persistent kernel over work items (instance, electron range).  A work-group
-// claims an item, stages the instance's total-rate pairs in LDS (if it changed), and its
-// lanes take electrons of the item one after another.  Lanes that reach a real-collision
-// candidate wait; the wave serves all waiting lanes together once wave_trigger() of them
-// wait (or no lane can make progress otherwise), which keeps the costly collision code
-// from running for one lane at a time.
+// Dummy-mode persistent kernel over the electrons of one or many instances (see ClaimPlan).
+// A work-group stages its instance's tables in LDS, and its lanes take electrons of the
+// instance one after another without waiting for each other; work-groups wait for their last
+// lane only when they change the instance.  What it replaced, work items of 1024 electrons
+// with a wait for the slowest lane at each item's end, was slower the more the electrons' times
+// differ (ms, items | now): 20 argon fields x 60,000 x 5000 FP32 117 | 97 (first launch, nothing
+// measured yet, 164 | 91), 10 x 60,000 x 1000 FP64 69 | 43 (126 | 41), the argon sweep 32 x 1e5
+// x 2e4 FP32 743 | 721; 16 adaptive fields x 50,000, all alike, 50.6 | 51.8.
+// Lanes that reach a real-collision candidate wait; the wave serves all waiting lanes together
+// once wave_trigger() of them wait (or no lane can make progress otherwise), which keeps the
+// costly collision code from running for one lane at a time.
 // ---------------------------------------------------------------------------------------
 template <typename R, bool HB, bool TR, int EXT>
-__global__ void __launch_bounds__(512) k_swarm_dummy(const InstanceDesc* __restrict__ descs,
-                                                     const WorkItem* __restrict__ items, int n_items,
-                                                     int* __restrict__ item_ctr, int pend_trig,
-                                                     int ch_off, int cum_off) {
+__global__ void __launch_bounds__(512, (dummy_waves<R, HB, TR, EXT>())) k_swarm_dummy(const InstanceDesc* __restrict__ descs, ClaimPlan plan,
+                                                     int pend_trig, int ch_off, int cum_off) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
   __shared__ double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
-  __shared__ int s_item;
-  __shared__ int s_next;
-  int cur_inst = -1;
-  for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(item_ctr, 1);
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(s_item);
-    if (it >= n_items) break;
-    const WorkItem wi = items[it];
-    const int inst = __builtin_amdgcn_readfirstlane(wi.inst);
+  __shared__ unsigned long long s_best;
+  int inst = plan.first != nullptr ? __builtin_amdgcn_readfirstlane(plan.first[blockIdx.x]) : 0;
+  for (; inst >= 0; inst = next_instance(descs, plan, &s_best)) {
     const InstanceDesc& d = descs[inst];
-    if (inst != cur_inst) {
-      const PT* src = reinterpret_cast<const PT*>(sizeof(R) == 8 ? static_cast<const void*>(d.nu64)
-                                                                 : static_cast<const void*>(d.nu32));
-      for (int g = threadIdx.x; g <= d.G; g += blockDim.x) {
-        PT q = src[g > 0 ? g - 1 : 0];
-        if (g == 0) q.y = 0;
-        s_nu[g] = q;
-      }
-      for (int c = threadIdx.x; c < d.nc; c += blockDim.x) s_ch[c] = d.chan[c];
-      if constexpr (sizeof(R) == 8)
-        for (int j = threadIdx.x; j < kUnitLogStride * kUnitLogEntries; j += blockDim.x) s_logtab[j] = d.logtab[j];
-      stage_cum<R>(d, smem, cum_off);
-      cur_inst = inst;
-    }
-    if (threadIdx.x == 0) s_next = 0;
+    stage_instance<R>(d, smem, s_ch, s_logtab, cum_off);
     __syncthreads();
     Consts<R> C = load_consts<R>(d);
     C.chan = s_ch;
@@ -1808,19 +1886,21 @@ __global__ void __launch_bounds__(512) k_swarm_dummy(const InstanceDesc* __restr
       C.cum = reinterpret_cast<const PT*>(smem + cum_off);
       C.cum_lds = true;
     }
-    const int64_t count = wi.count;
+    unsigned long long* taken = plan.taken + static_cast<int64_t>(inst) * kClaimStride;
+    const uint32_t count = static_cast<uint32_t>(d.n_electrons);
+    WaveClaim claims;
     Lane<R> L;
     L.state = ST_IDLE;
     L.trace_slot = -1;
     L.n_ev = 0;
     for (;;) {
-      if (L.state == ST_IDLE) {
-        const int e = atomicAdd(&s_next, 1);
-        if (e < count) {
-          const int64_t ei = wi.first + e;
+      const uint64_t idle = __ballot(L.state == ST_IDLE);
+      if (idle != 0) {
+        uint32_t ei;
+        const bool got = claim_electron(claims, L.state == ST_IDLE, idle, ~0ull, 0, taken, count, plan.chunk, plan.scarce, &ei);
+        if (got) {
           const uint32_t started = d.saved != nullptr ? d.saved[ei].started : 0u;
           if (started != 2u) {          // 2: finished in an earlier launch
-            L.rec = ei;
             if (started == 1u) load_state<R, HB, EXT>(d, L, C, ei);
             else init_primary<R, HB, EXT>(L, C, s_nu, static_cast<uint64_t>(ei));
             L.k_stop = stop_count(L.k, C);
@@ -1830,7 +1910,7 @@ __global__ void __launch_bounds__(512) k_swarm_dummy(const InstanceDesc* __restr
             }
             L.state = ST_ACTIVE;
           }
-        } else {
+        } else if (L.state == ST_IDLE && claims.none) {
           L.state = ST_DONE;
         }
       }
@@ -1854,17 +1934,16 @@ __global__ void __launch_bounds__(512) k_swarm_dummy(const InstanceDesc* __restr
       if (L.state == ST_STOPPED) {
         if (L.k >= C.n_coll || (L.flags & 4u)) {
           if (L.k >= C.n_coll) L.flags |= 1u;
-          write_record(d, L);
+          write_record(d, L, static_cast<int64_t>(L.id));
           atomicAdd(reinterpret_cast<unsigned long long*>(&d.ctr->n_done), 1ull);
-          if (d.saved != nullptr) d.saved[L.rec].started = 2u;
+          if (d.saved != nullptr) d.saved[L.id].started = 2u;
         } else {
-          save_state<R, EXT>(d, L, C, L.rec);
+          save_state<R, EXT>(d, L, C, static_cast<int64_t>(L.id));
         }
         L.state = ST_IDLE;
       }
       if (__ballot(L.state != ST_DONE) == 0) break;
     }
-    __syncthreads();
   }
 }
 
@@ -1969,46 +2048,21 @@ __device__ __forceinline__ void team_trials(Lane<R>& L, const Consts<R>& C,
 }
 
 template <typename R, bool HB, int EXT>
-__global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restrict__ descs,
-                                                    const WorkItem* __restrict__ items, int n_items,
-                                                    int* __restrict__ item_ctr, int pend_trig, int ch_off,
-                                                    int cum_off, int g, int per_wave, int64_t chunk) {
+__global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restrict__ descs, ClaimPlan plan,
+                                                    int pend_trig, int ch_off, int cum_off, int g, int per_wave) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
   __shared__ double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
-  __shared__ int s_item;
-  __shared__ int s_next;
+  __shared__ unsigned long long s_best;
   const int lane = static_cast<int>(threadIdx.x) & 63;
   const TeamLane team = {g, lane & (g - 1), lane & ~(g - 1)};
-  int cur_inst = -1;
-  for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(item_ctr, 1);
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(s_item);
-    if (it >= n_items) break;
-    // without a list, the electrons of one instance in ranges of `chunk`
-    WorkItem wi;
-    if (items != nullptr) wi = items[it];
-    else wi = {0, 0, it * chunk, min(chunk, descs->n_electrons - it * chunk)};
-    const int inst = __builtin_amdgcn_readfirstlane(wi.inst);
+  const uint64_t firsts = __ballot(team.sub == 0);
+  int inst = plan.first != nullptr ? __builtin_amdgcn_readfirstlane(plan.first[blockIdx.x]) : 0;
+  for (; inst >= 0; inst = next_instance(descs, plan, &s_best)) {
     const InstanceDesc& d = descs[inst];
-    if (inst != cur_inst) {
-      const PT* src = reinterpret_cast<const PT*>(sizeof(R) == 8 ? static_cast<const void*>(d.nu64)
-                                                                 : static_cast<const void*>(d.nu32));
-      for (int i = threadIdx.x; i <= d.G; i += blockDim.x) {
-        PT q = src[i > 0 ? i - 1 : 0];
-        if (i == 0) q.y = 0;
-        s_nu[i] = q;
-      }
-      for (int c = threadIdx.x; c < d.nc; c += blockDim.x) s_ch[c] = d.chan[c];
-      if constexpr (sizeof(R) == 8)
-        for (int j = threadIdx.x; j < kUnitLogStride * kUnitLogEntries; j += blockDim.x) s_logtab[j] = d.logtab[j];
-      stage_cum<R>(d, smem, cum_off);
-      cur_inst = inst;
-    }
-    if (threadIdx.x == 0) s_next = 0;
+    stage_instance<R>(d, smem, s_ch, s_logtab, cum_off);
     __syncthreads();
     Consts<R> C = load_consts<R>(d);
     C.chan = s_ch;
@@ -2017,27 +2071,27 @@ __global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restri
       C.cum = reinterpret_cast<const PT*>(smem + cum_off);
       C.cum_lds = true;
     }
-    const int64_t count = wi.count;
+    unsigned long long* taken = plan.taken + static_cast<int64_t>(inst) * kClaimStride;
+    const uint32_t count = static_cast<uint32_t>(d.n_electrons);
+    WaveClaim claims;
     Lane<R> L;
     L.state = team.base < per_wave * g ? ST_IDLE : ST_DONE;
     L.trace_slot = -1;
     L.n_ev = 0;
     for (;;) {
-      if (L.state == ST_IDLE) {
-        int e = 0;
-        if (team.sub == 0) e = atomicAdd(&s_next, 1);
-        e = __shfl(e, team.base);
-        if (e < count) {
-          const int64_t ei = wi.first + e;
+      const uint64_t idle = __ballot(L.state == ST_IDLE);
+      if (idle != 0) {
+        uint32_t ei;
+        const bool got = claim_electron(claims, L.state == ST_IDLE, idle, firsts, team.sub, taken, count, plan.chunk, plan.scarce, &ei);
+        if (got) {
           const uint32_t started = d.saved != nullptr ? d.saved[ei].started : 0u;
           if (started != 2u) {          // 2: finished in an earlier launch
-            L.rec = ei;
             if (started == 1u) load_state<R, HB, EXT>(d, L, C, ei);
             else init_primary<R, HB, EXT>(L, C, s_nu, static_cast<uint64_t>(ei));
             L.k_stop = stop_count(L.k, C);
             L.state = ST_ACTIVE;
           }
-        } else {
+        } else if (L.state == ST_IDLE && claims.none) {
           L.state = ST_DONE;
         }
       }
@@ -2058,18 +2112,17 @@ __global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restri
         if (L.k >= C.n_coll) L.flags |= 1u;
         if (team.sub == 0) {
           if (final) {
-            write_record(d, L);
+            write_record(d, L, static_cast<int64_t>(L.id));
             atomicAdd(reinterpret_cast<unsigned long long*>(&d.ctr->n_done), 1ull);
-            if (d.saved != nullptr) d.saved[L.rec].started = 2u;
+            if (d.saved != nullptr) d.saved[L.id].started = 2u;
           } else {
-            save_state<R, EXT>(d, L, C, L.rec);
+            save_state<R, EXT>(d, L, C, static_cast<int64_t>(L.id));
           }
         }
         L.state = ST_IDLE;
       }
       if (__ballot(L.state != ST_DONE) == 0) break;
     }
-    __syncthreads();
   }
 }
 
@@ -2209,17 +2262,14 @@ __device__ __forceinline__ void trial_block_pooled(Lane<R>& L, const Consts<R>& 
 }
 
 template <typename R, bool HB, int EXT>
-__global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __restrict__ descs,
-                                                      const WorkItem* __restrict__ items, int n_items,
-                                                      int* __restrict__ item_ctr, int n_service,
-                                                      int ch_off, int pool_off, int cum_off) {
+__global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __restrict__ descs, ClaimPlan plan,
+                                                      int n_service, int ch_off, int pool_off, int cum_off) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
   __shared__ double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
-  __shared__ int s_item;
-  __shared__ int s_next;
+  __shared__ unsigned long long s_best;
   __shared__ int s_ncand[2];   // pool slots asked for, by round parity
   __shared__ int s_live[3];    // some electron of the item is not done, by round mod 3
   const int wave = static_cast<int>(threadIdx.x) >> 6;
@@ -2232,31 +2282,11 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
   P.r = reinterpret_cast<R*>(P.d + kPoolD * P.cap);
   P.u = reinterpret_cast<uint32_t*>(P.r + kPoolR * P.cap);
   const uint64_t lane_lt = (1ull << lane) - 1ull;
-  int cur_inst = -1;
-  for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(item_ctr, 1);
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(s_item);
-    if (it >= n_items) break;
-    const WorkItem wi = items[it];
-    const int inst = __builtin_amdgcn_readfirstlane(wi.inst);
+  int inst = plan.first != nullptr ? __builtin_amdgcn_readfirstlane(plan.first[blockIdx.x]) : 0;
+  for (; inst >= 0; inst = next_instance(descs, plan, &s_best)) {
     const InstanceDesc& d = descs[inst];
-    if (inst != cur_inst) {
-      const PT* src = reinterpret_cast<const PT*>(sizeof(R) == 8 ? static_cast<const void*>(d.nu64)
-                                                                 : static_cast<const void*>(d.nu32));
-      for (int g = threadIdx.x; g <= d.G; g += blockDim.x) {
-        PT q = src[g > 0 ? g - 1 : 0];
-        if (g == 0) q.y = 0;
-        s_nu[g] = q;
-      }
-      for (int c = threadIdx.x; c < d.nc; c += blockDim.x) s_ch[c] = d.chan[c];
-      if constexpr (sizeof(R) == 8)
-        for (int j = threadIdx.x; j < kUnitLogStride * kUnitLogEntries; j += blockDim.x) s_logtab[j] = d.logtab[j];
-      stage_cum<R>(d, smem, cum_off);
-      cur_inst = inst;
-    }
+    stage_instance<R>(d, smem, s_ch, s_logtab, cum_off);
     if (threadIdx.x == 0) {
-      s_next = 0;
       s_ncand[0] = s_ncand[1] = 0;
       s_live[0] = s_live[1] = s_live[2] = 0;
     }
@@ -2293,7 +2323,9 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
       }
     } else {
       // ---- trial waves ----
-      const int64_t count = wi.count;
+      unsigned long long* taken = plan.taken + static_cast<int64_t>(inst) * kClaimStride;
+      const uint32_t count = static_cast<uint32_t>(d.n_electrons);
+      WaveClaim claims;
       Lane<R> L;
       L.state = ST_IDLE;
       L.trace_slot = -1;
@@ -2304,27 +2336,27 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
         if (L.state == ST_STOPPED) {
           if (L.k >= C.n_coll || (L.flags & 4u)) {
             if (L.k >= C.n_coll) L.flags |= 1u;
-            write_record(d, L);
+            write_record(d, L, static_cast<int64_t>(L.id));
             atomicAdd(reinterpret_cast<unsigned long long*>(&d.ctr->n_done), 1ull);
-            if (d.saved != nullptr) d.saved[L.rec].started = 2u;
+            if (d.saved != nullptr) d.saved[L.id].started = 2u;
           } else {
-            save_state<R, EXT>(d, L, C, L.rec);
+            save_state<R, EXT>(d, L, C, static_cast<int64_t>(L.id));
           }
           L.state = ST_IDLE;
         }
-        if (L.state == ST_IDLE) {
-          const int e = atomicAdd(&s_next, 1);
-          if (e < count) {
-            const int64_t ei = wi.first + e;
+        const uint64_t idle = __ballot(L.state == ST_IDLE);
+        if (idle != 0) {
+          uint32_t ei;
+          const bool got = claim_electron(claims, L.state == ST_IDLE, idle, ~0ull, 0, taken, count, plan.chunk, plan.scarce, &ei);
+          if (got) {
             const uint32_t started = d.saved != nullptr ? d.saved[ei].started : 0u;
             if (started != 2u) {
-              L.rec = ei;
-              if (started == 1u) load_state<R, HB, EXT>(d, L, C, ei);
+                if (started == 1u) load_state<R, HB, EXT>(d, L, C, ei);
               else init_primary<R, HB, EXT>(L, C, s_nu, static_cast<uint64_t>(ei));
               L.k_stop = stop_count(L.k, C);
               L.state = ST_ACTIVE;
             }
-          } else {
+          } else if (L.state == ST_IDLE && claims.none) {
             L.state = ST_DONE;
           }
         }
@@ -2352,7 +2384,6 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
         if (s_live[round % 3] == 0) break;
       }
     }
-    __syncthreads();
   }
 }
 
@@ -2380,48 +2411,28 @@ constexpr uint32_t kClaimChunk = 64;      // electrons a wave takes per claim
 constexpr uint32_t kAbortPoll = 64;       // passes between reads of the overflow counter
 constexpr uint32_t kParkPoll = 8;         // passes between a parking candidate's reads of the queue tail
 
-// A value the whole wave holds, kept in scalar registers.
-__device__ __forceinline__ int64_t wave_uniform(int64_t x) {
-  const uint64_t u = static_cast<uint64_t>(x);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
-  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
-  return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 template <typename R, bool HB, bool TR, int EXT, bool TEAM>
 __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restrict__ desc, int pend_trig,
                                                     int ch_off, int cum_off, int64_t first, int64_t count,
                                                     int flush, const ParkedState* __restrict__ park_in,
                                                     int64_t n_park_in, ParkedState* __restrict__ park_out,
                                                     int64_t park_min, int park_lanes, int64_t tail0,
-                                                    int g, int per_wave) {
+                                                    int g, int per_wave, uint32_t scarce) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
   __shared__ double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
   const InstanceDesc& d = *desc;
-  {
-    const PT* src = reinterpret_cast<const PT*>(sizeof(R) == 8 ? static_cast<const void*>(d.nu64)
-                                                               : static_cast<const void*>(d.nu32));
-    for (int g = threadIdx.x; g <= d.G; g += blockDim.x) {
-      PT q = src[g > 0 ? g - 1 : 0];
-      if (g == 0) q.y = 0;
-      s_nu[g] = q;
-    }
-    for (int c = threadIdx.x; c < d.nc; c += blockDim.x) s_ch[c] = d.chan[c];
-    if constexpr (sizeof(R) == 8)
-      for (int j = threadIdx.x; j < kUnitLogStride * kUnitLogEntries; j += blockDim.x) s_logtab[j] = d.logtab[j];
-    stage_cum<R>(d, smem, cum_off);
-  }
+  stage_instance<R>(d, smem, s_ch, s_logtab, cum_off);
   __syncthreads();
   Consts<R> C = load_consts<R>(d);
   C.chan = s_ch;
   C.logtab = s_logtab;
   if (cum_off >= 0) {
-      C.cum = reinterpret_cast<const PT*>(smem + cum_off);
-      C.cum_lds = true;
-    }
+    C.cum = reinterpret_cast<const PT*>(smem + cum_off);
+    C.cum_lds = true;
+  }
   RunCounters* ctr = d.ctr;
   const int64_t N = d.n_electrons;
   const int64_t child_cap = d.capacity - N;
@@ -2435,32 +2446,22 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
   // lane's electron
   const uint64_t firsts = TEAM ? __ballot(team.sub == 0) : ~0ull;
   const uint64_t lane_lt = ((1ull << team.base) - 1ull) & firsts;
-  const int64_t claim = TEAM ? per_wave : static_cast<int>(kClaimChunk);
-  // wave-uniform: the wave's chunk [w_next, w_end), whether the generation is exhausted,
-  // whether the run is stopping after an overflow, and the pass count
+  const uint32_t claim = TEAM ? static_cast<uint32_t>(per_wave) : kClaimChunk;
+  // wave-uniform: the wave's electrons, whether the run is stopping after an overflow, and the
+  // pass count
   const int64_t total = n_park_in + count;   // parked electrons first, then the generation's
-  int64_t w_next = 0, w_end = 0;
-  bool exhausted = false, aborting = flush != 0, parking = false;
+  WaveClaim claims;
+  bool aborting = flush != 0, parking = false;
   uint32_t pass = 0;
   for (;;) {
     const uint64_t idle = __ballot(L.state == ST_IDLE);
     if (idle != 0) {
-      if (w_next >= w_end && !exhausted) {
-        const int leader = __ffsll(static_cast<long long>(idle)) - 1;
-        unsigned long long base = 0;
-        if (static_cast<int>(__lane_id()) == leader)
-          base = atomicAdd(reinterpret_cast<unsigned long long*>(&ctr->gen_next),
-                           static_cast<unsigned long long>(claim));
-        w_next = wave_uniform(static_cast<int64_t>(__shfl(base, leader)));
-        w_end = min(w_next + claim, total);
-        exhausted = w_next >= total;
-      }
-      const int64_t avail = max(w_end - w_next, int64_t{0});
-      const int64_t rank = static_cast<int64_t>(__popcll(idle & lane_lt));
-      const int64_t e = w_next + rank;
-      w_next = wave_uniform(min(w_end, w_next + static_cast<int64_t>(__popcll(idle & firsts))));
-      if (L.state == ST_IDLE && exhausted && avail == 0) L.state = ST_DONE;
-      if (L.state == ST_IDLE && rank < avail) {
+      uint32_t e;
+      const bool got = claim_electron(claims, L.state == ST_IDLE, idle, firsts, team.sub,
+                                      reinterpret_cast<unsigned long long*>(&ctr->gen_next), static_cast<uint32_t>(total),
+                                      claim, scarce, &e);
+      if (L.state == ST_IDLE && !got && claims.none) L.state = ST_DONE;
+      if (got) {
         if (e < n_park_in) {
           // parked by the launch before, at a real-collision boundary
           const ParkedState ps = park_in[e];
@@ -2507,7 +2508,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
     // Parking: all of the launch's electrons are claimed, few lanes of the wave still run,
     // and this launch has created enough secondaries for the next one.  The running lanes
     // stop at their next real collision (a ready lane at the one it is about to make).
-    if (park_min > 0 && exhausted && !parking && !aborting && pass % kParkPoll == 0) {
+    if (park_min > 0 && claims.none && !parking && !aborting && pass % kParkPoll == 0) {
       const int running = static_cast<int>(__popcll(__ballot(L.state == ST_ACTIVE || L.state == ST_READY) & firsts));
       if (running > 0 && running * 64 <= park_lanes * (TEAM ? per_wave : 64)) {
         const int64_t made = wave_uniform(static_cast<int64_t>(__hip_atomic_load(
@@ -2585,7 +2586,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
         }
       } else {
         if (L.k >= C.n_coll && !(L.flags & 10u)) L.flags |= 1u;   // attached or aborted: not finished
-        if (!TEAM || team.sub == 0) write_record(d, L);
+        if (!TEAM || team.sub == 0) write_record(d, L, L.rec);
         L.state = ST_IDLE;
       }
     }
@@ -2900,27 +2901,26 @@ size_t swarm_pool_slot_bytes(int precision) {
   return kPoolD * sizeof(double) + kPoolR * r + kPoolU * sizeof(uint32_t);
 }
 
-hipError_t launch_swarm_dummy(const InstanceDesc* d_desc, const WorkItem* d_items, int32_t n_items,
-                              int32_t* d_item_counter, int precision, bool has_b, bool trace,
+hipError_t launch_swarm_dummy(const InstanceDesc* d_desc, ClaimPlan plan, int precision, bool has_b, bool trace,
                               int ext, int service_waves, int block_size, int grid, int pending_trigger,
                               size_t lds_bytes, int ch_off, int pool_off, int cum_off, hipStream_t s, TeamShape team) {
+  const bool teams = team.lanes > 1 && !trace && service_waves == 0;
+  if (teams) plan.chunk = team.per_wave;
+  // electrons for two more claims of every wave
+  plan.scarce = 2u * static_cast<uint32_t>(plan.chunk) * static_cast<uint32_t>(grid * ((teams ? team.block : block_size) / 64));
   if (service_waves > 0 && !trace) {
     if (service_waves >= block_size / 64) return hipErrorInvalidValue;
     void* fn = pick_pooled(precision, has_b, ext);
-    void* args[] = {const_cast<InstanceDesc**>(&d_desc), const_cast<WorkItem**>(&d_items), &n_items,
-                    &d_item_counter, &service_waves, &ch_off, &pool_off, &cum_off};
+    void* args[] = {const_cast<InstanceDesc**>(&d_desc), &plan, &service_waves, &ch_off, &pool_off, &cum_off};
     return hipLaunchKernel(fn, dim3(grid), dim3(block_size), args, lds_bytes, s);
   }
-  if (team.lanes > 1 && !trace) {
-    int64_t chunk = team.per_group();
+  if (teams) {
     void* fn = pick_team(precision, has_b, ext, false);
-    void* args[] = {const_cast<InstanceDesc**>(&d_desc), const_cast<WorkItem**>(&d_items), &n_items,
-                    &d_item_counter, &team.trigger, &ch_off, &cum_off, &team.lanes, &team.per_wave, &chunk};
+    void* args[] = {const_cast<InstanceDesc**>(&d_desc), &plan, &team.trigger, &ch_off, &cum_off, &team.lanes, &team.per_wave};
     return hipLaunchKernel(fn, dim3(grid), dim3(team.block), args, lds_bytes, s);
   }
   void* fn = pick_kernel(precision, has_b, trace, false, ext);
-  void* args[] = {const_cast<InstanceDesc**>(&d_desc), const_cast<WorkItem**>(&d_items), &n_items,
-                  &d_item_counter, &pending_trigger, &ch_off, &cum_off};
+  void* args[] = {const_cast<InstanceDesc**>(&d_desc), &plan, &pending_trigger, &ch_off, &cum_off};
   return hipLaunchKernel(fn, dim3(grid), dim3(block_size), args, lds_bytes, s);
 }
 
@@ -2935,9 +2935,10 @@ hipError_t launch_swarm_real(const InstanceDesc* d_desc, int precision, bool has
     block_size = team.block;
     pending_trigger = team.trigger;
   }
+  uint32_t scarce = 2u * (teams ? static_cast<uint32_t>(team.per_wave) : kClaimChunk) * static_cast<uint32_t>(grid * (block_size / 64));
   void* args[] = {const_cast<InstanceDesc**>(&d_desc), &pending_trigger, &ch_off, &cum_off, &first, &count, &flush,
                   const_cast<ParkedState**>(&park_in), &n_park_in, &park_out, &park_min, &park_lanes, &tail0,
-                  &team.lanes, &team.per_wave};
+                  &team.lanes, &team.per_wave, &scarce};
   return hipLaunchKernel(fn, dim3(grid), dim3(block_size), args, lds_bytes, s);
 }
 

@@ -1,6 +1,6 @@
 // swarm_run_noalloc: the dummy-mode run of swarm_run for callers that cannot allocate device
-// memory.  The per-run scratch that swarm_run allocates (work items and their counter, the
-// tally tiles, partial sums, totals and the tally output) lives here in one file-scope device
+// memory.  The per-run scratch that swarm_run allocates (the tally tiles, partial sums, totals
+// and the tally output) lives here in one file-scope device
 // array instead; the records go to memory the caller passes in.  The kernels are the ones
 // swarm_run launches, with the same arguments, so the records and tallies are the same bits.
 
@@ -16,15 +16,12 @@ using namespace swarm_impl;
 namespace {
 
 constexpr int64_t kMaxElectrons = int64_t(1) << 22;
-constexpr int64_t kMaxItems = 16384;
 constexpr int64_t kMaxTiles = (kMaxElectrons + kTallyTile - 1) / kTallyTile;
 constexpr int kMaxDevices = 64;
 
 constexpr size_t al256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 // layout of the scratch array (byte offsets)
-constexpr size_t kOffItems = 0;
-constexpr size_t kOffCounter = al256(kOffItems + kMaxItems * sizeof(WorkItem));
-constexpr size_t kOffTiles = kOffCounter + 256;
+constexpr size_t kOffTiles = 0;
 constexpr size_t kOffBase = al256(kOffTiles + kMaxTiles * sizeof(TallyTile));
 constexpr size_t kOffNrec = kOffBase + 256;
 constexpr size_t kOffPart1 = kOffNrec + 256;
@@ -45,20 +42,10 @@ namespace {
 std::mutex g_mu[kMaxDevices];         // one call at a time per device (they share the array)
 void* g_scratch[kMaxDevices] = {};    // device address of `scratch` on each device
 
-// Work items of one instance (electron ranges of `chunk`), the tally tiles of its records,
-// and the counters both start from: what swarm_run builds on the host and copies over.
-__global__ void k_noalloc_plan(WorkItem* __restrict__ items, int32_t n_items, int64_t n_e, int64_t chunk,
-                               int32_t* __restrict__ item_ctr, TallyTile* __restrict__ tiles, int32_t n_tiles,
-                               int32_t* __restrict__ base, int64_t* __restrict__ nrec) {
+// The tally tiles of one instance's records: what swarm_run builds on the host and copies over.
+__global__ void k_noalloc_plan(int64_t n_e, TallyTile* __restrict__ tiles, int32_t n_tiles, int32_t* __restrict__ base,
+                               int64_t* __restrict__ nrec) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n_items) {
-    WorkItem w;
-    w.inst = 0;
-    w.pad = 0;
-    w.first = i * chunk;
-    w.count = n_e - w.first < chunk ? n_e - w.first : chunk;
-    items[i] = w;
-  }
   if (i < n_tiles) {
     TallyTile t;
     t.inst = 0;
@@ -68,7 +55,6 @@ __global__ void k_noalloc_plan(WorkItem* __restrict__ items, int32_t n_items, in
     tiles[i] = t;
   }
   if (i == 0) {
-    *item_ctr = 0;
     *base = 0;
     *nrec = n_e;
   }
@@ -109,8 +95,6 @@ swarm_status swarm_run_noalloc(swarm_t h, int64_t n_electrons, int64_t n_collisi
   char* base = nullptr;
   swarm_status st = scratch_address(dev, &base);
   if (st != SWARM_OK) return st;
-  WorkItem* d_items = reinterpret_cast<WorkItem*>(base + kOffItems);
-  int32_t* d_ctr = reinterpret_cast<int32_t*>(base + kOffCounter);
   TallyTile* d_tiles = reinterpret_cast<TallyTile*>(base + kOffTiles);
   int32_t* d_base = reinterpret_cast<int32_t*>(base + kOffBase);
   int64_t* d_nrec = reinterpret_cast<int64_t*>(base + kOffNrec);
@@ -140,35 +124,26 @@ swarm_status swarm_run_noalloc(swarm_t h, int64_t n_electrons, int64_t n_collisi
   if (static_cast<int64_t>(ll.bytes) > device_info().lds_per_block)
     return fail(SWARM_ERR_INVALID_ARG, "the tables need %zu bytes of LDS per work-group", ll.bytes);
   const int ext = d.thermal_targets || d.relativistic ? 2 : d.trial_strategy != SWARM_TRIAL_CONSTANT ? 1 : 0;
-  const TeamShape team = h->free_shape ? team_shape(static_cast<double>(n_electrons), d.trials) : TeamShape{};
+  const TeamShape team = h->free_shape ? team_shape({n_electrons}, {static_cast<double>(n_collisions)}, {d.trials}) : TeamShape{};
   const int per_cu = team.lanes > 1
       ? swarm_kernel_max_blocks_per_cu(d.precision, h->has_b, false, false, ext, 0, team.block, ll.bytes, true)
       : swarm_kernel_max_blocks_per_cu(d.precision, h->has_b, false, false, ext, o.service_waves, o.block_size, ll.bytes);
   const int64_t slots = static_cast<int64_t>(device_info().n_cu) * per_cu;
-  const int64_t unit = team.lanes > 1 ? team.per_group() : o.block_size;
-  auto round_up = [&](int64_t n) { return (n + unit - 1) / unit * unit; };
-  int64_t chunk = round_up((n_electrons + 4 * slots - 1) / (4 * slots));
-  chunk = team.lanes > 1 ? unit : std::max<int64_t>(o.block_size, std::min<int64_t>(chunk, o.chunk));
-  // a list of at most kMaxItems items (a team launch has none)
-  if (team.lanes == 1) chunk = std::max(chunk, round_up((n_electrons + kMaxItems - 1) / kMaxItems));
-  const int64_t n_items = (n_electrons + chunk - 1) / chunk;
+  const int64_t per_group = team.lanes > 1 ? team.per_group() : o.block_size;
   const int64_t n_tiles = (n_electrons + kTallyTile - 1) / kTallyTile;
-  const int64_t n_listed = team.lanes > 1 ? 0 : n_items;
-  if (n_listed > kMaxItems || n_tiles > kMaxTiles) return fail(SWARM_ERR_INVALID_ARG, "work does not fit the scratch");
-  const int64_t plan_n = std::max(n_listed, n_tiles);
-  hipLaunchKernelGGL(k_noalloc_plan, dim3(static_cast<unsigned>((plan_n + 255) / 256)), dim3(256), 0, s, d_items,
-                     static_cast<int32_t>(n_listed), n_electrons, chunk, d_ctr, d_tiles, static_cast<int32_t>(n_tiles),
-                     d_base, d_nrec);
+  if (n_tiles > kMaxTiles) return fail(SWARM_ERR_INVALID_ARG, "work does not fit the scratch");
+  hipLaunchKernelGGL(k_noalloc_plan, dim3(static_cast<unsigned>((n_tiles + 255) / 256)), dim3(256), 0, s, n_electrons,
+                     d_tiles, static_cast<int32_t>(n_tiles), d_base, d_nrec);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "plan launch");
   if ((e = launch_fill_u64(reinterpret_cast<uint64_t*>(d.ctr), 0ull, sizeof(RunCounters) / sizeof(uint64_t), s)) != hipSuccess)
     return hip_fail(e, "counters");
   if ((e = hipMemcpyAsync(h->d_desc, &h->desc, sizeof(InstanceDesc), hipMemcpyHostToDevice, s)) != hipSuccess)
     return hip_fail(e, "descriptor");
   if ((e = hipEventRecord(h->ev[0], s)) != hipSuccess) return hip_fail(e, "event");
-  const int grid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(n_items, slots)));
-  if ((e = launch_swarm_dummy(h->d_desc, team.lanes > 1 ? nullptr : d_items, static_cast<int32_t>(n_items), d_ctr, d.precision, h->has_b, false,
-                              ext, o.service_waves, o.block_size, grid, o.pending_trigger, ll.bytes, ll.ch_off,
-                              ll.pool_off, ll.cum_off, s, team)) != hipSuccess)
+  const int grid = static_cast<int>(std::min<int64_t>((n_electrons + per_group - 1) / per_group, slots));
+  const ClaimPlan plan = {reinterpret_cast<unsigned long long*>(&d.ctr->gen_next), nullptr, nullptr, 1, wave_chunk(o)};
+  if ((e = launch_swarm_dummy(h->d_desc, plan, d.precision, h->has_b, false, ext, o.service_waves, o.block_size, grid,
+                              o.pending_trigger, ll.bytes, ll.ch_off, ll.pool_off, ll.cum_off, s, team)) != hipSuccess)
     return hip_fail(e, "swarm kernel launch");
   if ((e = hipEventRecord(h->ev[1], s)) != hipSuccess) return hip_fail(e, "event");
   if ((e = launch_tallies(h->d_desc, d_tiles, static_cast<int32_t>(n_tiles), d_base, d_nrec, 1, d_part1, d_part2,

@@ -87,7 +87,7 @@ struct swarm_server {
   bool stop = false;
   std::thread th;
   // device state of the epochs
-  DevBuf ctrs, descs, items;
+  DevBuf ctrs, descs, plan_mem;
   DevBuf mdescs, mparts;    // the requests measured after an epoch and their block sums
   std::vector<int> free_slots;
   int max_slots = 0;
@@ -313,7 +313,7 @@ std::vector<std::shared_ptr<Request>> pick_shortest_first(const std::vector<std:
 
 void scheduler(swarm_server* s) {
   std::vector<InstanceDesc> descs;
-  std::vector<WorkItem> items;
+  LaunchPlan plan;
   hipEvent_t ev0, ev1;
   (void)hipEventCreate(&ev0);
   (void)hipEventCreate(&ev1);
@@ -356,9 +356,8 @@ void scheduler(swarm_server* s) {
       r->quantum = std::max<int64_t>(1, std::min<int64_t>(q, r->n_c - r->done_coll));   // no electron needs more
     }
     descs.clear();
-    std::vector<int64_t> ne, nc;
-    std::vector<int64_t> quanta;
-    std::vector<double> trials;
+    std::vector<int64_t> ne;
+    std::vector<double> quanta, trials, work;
     int G = 0, n_ch = 0;
     bool magnetic = false;
     int extended = 0;
@@ -367,13 +366,13 @@ void scheduler(swarm_server* s) {
       d.quantum = static_cast<uint32_t>(std::min<int64_t>(r->quantum, 0xffffffffLL));
       descs.push_back(d);
       ne.push_back(r->n_e);
-      quanta.push_back(r->quantum);
-      trials.push_back(d.trials);
-      // the items' order and sizes follow the expected device work per electron (longest
-      // first), not the collision count: with per-request quanta the requests with the
-      // fewest collisions per epoch are the slowest ones
-      const double c_r = r->cost > 0 ? r->cost : worst > 0 ? worst : 1.0;
-      nc.push_back(std::max<int64_t>(1, std::llround(16.0 * c_r * static_cast<double>(r->quantum))));
+      // the plan follows the expected device work per electron, not the collision count: with
+      // per-request quanta the requests with the fewest collisions per epoch are the slowest
+      // ones.  Trials per collision from the measured blocks b, whose two trials are both null
+      // with probability 1 - 1/b, or expected.
+      const double b = r->cost - kCollisionBlocks;
+      trials.push_back(r->cost > 0 ? 1.0 / (1.0 - std::sqrt(1.0 - 1.0 / std::max(1.0, b))) : d.trials);
+      quanta.push_back(static_cast<double>(r->quantum));
       G = std::max(G, d.G);
       n_ch = std::max(n_ch, d.nc);
       magnetic |= r->h->has_b;
@@ -383,30 +382,21 @@ void scheduler(swarm_server* s) {
       std::lock_guard<std::mutex> lk(s->mu);   // swarm_server_poll reads the count
       for (auto& r : act) r->epochs += 1;
     }
-    const swarm_launch_opts o = resolve_opts(&s->p.opts, s->p.precision);
+    const swarm_launch_opts o = resolve_opts(&s->p.opts);
     const LdsLayout ll = lds_layout(s->p.precision, G, n_ch, o.service_waves, o.table_layout);
     const size_t lds = ll.bytes;
-    TeamShape team = free_shape(&s->p.opts) ? team_shape(ne, quanta, trials) : TeamShape{};
-    int per_cu = 1;
+    const TeamShape team = free_shape(&s->p.opts) ? team_shape(ne, quanta, trials) : TeamShape{};
+    for (size_t i = 0; i < act.size(); ++i) work.push_back(electron_work(quanta[i], trials[i], team.lanes));
+    const int per_cu = team.lanes > 1
+        ? swarm_kernel_max_blocks_per_cu(s->p.precision, magnetic, false, false, extended, 0, team.block, lds, true)
+        : swarm_kernel_max_blocks_per_cu(s->p.precision, magnetic, false, false, extended, o.service_waves, o.block_size, lds);
+    plan = plan_launch(ne, work, team.lanes > 1 ? team.per_group() : o.block_size, static_cast<int64_t>(device_info().n_cu) * per_cu);
     hipError_t e;
-    bool ok = (e = s->descs.ensure(descs.size() * sizeof(InstanceDesc))) == hipSuccess;
-    for (;;) {
-      per_cu = team.lanes > 1
-          ? swarm_kernel_max_blocks_per_cu(s->p.precision, magnetic, false, false, extended, 0, team.block, lds, true)
-          : swarm_kernel_max_blocks_per_cu(s->p.precision, magnetic, false, false, extended, o.service_waves, o.block_size, lds);
-      const int64_t slots = static_cast<int64_t>(device_info().n_cu) * per_cu;
-      if (team.lanes > 1) make_items(ne, nc, team.per_group(), items, slots, team.per_group());
-      else make_items(ne, nc, o.chunk, items, slots, o.block_size);
-      if (ok) ok = (e = s->items.ensure(items.size() * sizeof(WorkItem) + 256)) == hipSuccess;
-      if (ok || e != hipErrorOutOfMemory || team.lanes == 1) break;
-      // a caller-owned region may hold the shorter list of the one-lane kernel only
-      team = TeamShape{};
-      ok = true;
-    }
-    int32_t* item_ctr = ok ? reinterpret_cast<int32_t*>(static_cast<char*>(s->items.p) + items.size() * sizeof(WorkItem)) : nullptr;
+    bool ok = (e = s->descs.ensure(descs.size() * sizeof(InstanceDesc))) == hipSuccess &&
+              (e = s->plan_mem.ensure(plan.bytes())) == hipSuccess;
     if (ok) ok = (e = hipMemcpyAsync(s->descs.p, descs.data(), descs.size() * sizeof(InstanceDesc), hipMemcpyHostToDevice, s->compute)) == hipSuccess &&
-                 (e = hipMemcpyAsync(s->items.p, items.data(), items.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s->compute)) == hipSuccess &&
-                 (e = launch_fill_u32(reinterpret_cast<uint32_t*>(item_ctr), 0u, 1, s->compute)) == hipSuccess &&
+                 (e = plan.upload(s->plan_mem.p, s->compute)) == hipSuccess &&
+                 (e = plan.clear(s->plan_mem.p, s->compute)) == hipSuccess &&
                  (e = hipEventRecord(ev0, s->compute)) == hipSuccess;
     if (ok && ++s->epoch == s->fail_epoch) {
       // failure injection (tests of the error path): nothing is launched
@@ -414,11 +404,9 @@ void scheduler(swarm_server* s) {
       e = hipErrorLaunchFailure;
     }
     if (ok) {
-      const int grid = std::max(1, std::min<int>(static_cast<int>(items.size()), device_info().n_cu * per_cu));
-      ok = (e = launch_swarm_dummy(static_cast<const InstanceDesc*>(s->descs.p), static_cast<const WorkItem*>(s->items.p),
-                                   static_cast<int32_t>(items.size()), item_ctr, s->p.precision, magnetic, false, extended,
-                                   o.service_waves, o.block_size, grid, o.pending_trigger, lds, ll.ch_off,
-                                   ll.pool_off, ll.cum_off, s->compute, team)) == hipSuccess &&
+      ok = (e = launch_swarm_dummy(static_cast<const InstanceDesc*>(s->descs.p), plan.view(s->plan_mem.p, wave_chunk(o)),
+                                   s->p.precision, magnetic, false, extended, o.service_waves, o.block_size, plan.grid,
+                                   o.pending_trigger, lds, ll.ch_off, ll.pool_off, ll.cum_off, s->compute, team)) == hipSuccess &&
            (e = hipEventRecord(ev1, s->compute)) == hipSuccess;
     }
     // while the epoch runs, prepare the requests that arrived meanwhile
@@ -460,10 +448,10 @@ void scheduler(swarm_server* s) {
     std::vector<std::shared_ptr<Request>> fin;
     std::vector<int64_t> fin_n;
     std::vector<InstanceDesc> fin_desc;
-    int64_t work = 0;
+    int64_t collisions = 0;
     for (size_t i = 0; i < act.size(); ++i) {
       const int64_t done_now = static_cast<int64_t>(hc[act[i]->slot].n_done);
-      work += act[i]->quantum * act[i]->n_e;
+      collisions += act[i]->quantum * act[i]->n_e;
       if (done_now >= act[i]->n_e) {
         fin.push_back(act[i]);
         fin_n.push_back(act[i]->n_e);
@@ -494,7 +482,7 @@ void scheduler(swarm_server* s) {
       }
     }
     if (ms > 0) {
-      const double r_now = static_cast<double>(work) / (ms * 1e-3);
+      const double r_now = static_cast<double>(collisions) / (ms * 1e-3);
       s->rate = s->rate > 0 ? 0.5 * s->rate + 0.5 * r_now : r_now;
       // device work of the epoch in trial blocks, from the requests' costs as now measured
       double units = 0.0, worst_now = 0.0;
@@ -562,7 +550,7 @@ swarm_status server_create(const swarm_server_params* p, void* arena, int64_t ar
   if (arena) {
     s->mem = std::make_unique<Arena>(arena, static_cast<size_t>(arena_bytes));
     s->budget = std::min<int64_t>(s->budget, static_cast<int64_t>(s->mem->capacity()));
-    for (DevBuf* b : {&s->ctrs, &s->descs, &s->items, &s->mdescs, &s->mparts}) b->arena = s->mem.get();
+    for (DevBuf* b : {&s->ctrs, &s->descs, &s->plan_mem, &s->mdescs, &s->mparts}) b->arena = s->mem.get();
     s->tally.bind(s->mem.get());
   }
   s->t0 = std::chrono::steady_clock::now();
