@@ -304,7 +304,7 @@ swarm_status swarm_tables(swarm_t h, int32_t* grid_size, int32_t* n_channels, do
 swarm_status swarm_last_timing(swarm_t h, double* kernel_ms, double* total_ms);
 
 /* Launches of the last run's simulation kernel (one in DUMMY mode; in REAL mode one per
- * generation, and more where the stragglers of a launch were parked for the next one, see
+ * generation, and more where electrons of a launch were parked for the next one, see
  * swarm_launch_opts.park_lanes) and the electrons parked between them in all.  Either pointer
  * may be NULL.  SWARM_ERR_STATE before the first completed run. */
 swarm_status swarm_last_launches(swarm_t h, int64_t* launches, int64_t* parked);
@@ -357,8 +357,10 @@ typedef struct {
   int32_t park_lanes;      /* real secondaries: once all electrons of a launch are claimed, a
                               wave with at most this many running lanes parks them (each at its
                               next real collision) for the next launch, if the launch has
-                              created secondaries for an eighth of the device; 0: 32, -1: never,
-                              at most 64 */
+                              created secondaries for an eighth of the device; 0: 32, at most
+                              64.  -1: never, and launches of few electrons, which otherwise
+                              run in slices of the budget and are parked in between, run whole
+                              generations */
 } swarm_launch_opts;
 
 /* Launch shape of the handle's own runs (swarm_run); zero fields take the defaults.  Like
@@ -369,7 +371,7 @@ typedef struct swarm_batch* swarm_batch_t;
 
 /* A batch of instances (all DUMMY mode, all the same precision) with one job each.  The
  * batch keeps the per-instance results on the device; swarm_batch_launch runs every job
- * in one persistent kernel (work items of `chunk` electrons, instance tables staged in
+ * in one persistent kernel (waves claim `chunk` electrons at a time, instance tables staged in
  * LDS), followed by the tally kernels, captured in a hipGraph when use_graph != 0.  The
  * first launch hands out the instances' items heaviest collision budget first, then in the
  * order given; swarm_batch_wait of the first launch orders them again by each instance's

@@ -855,37 +855,63 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     // appended to the queue (slots [first, first + count)), until a generation creates none.
     // Every generation starts at least one collision later in its lineage budget than the
     // one before, so there are at most n_collisions + 1.  After an overflow the next launch
-    // records the queued secondaries unstarted (flag 8) and creates none.  A launch that has
-    // created secondaries for at least an eighth of the device's lanes lets its last few
-    // running electrons park, and the next launch resumes them first (1e6 primaries of the
-    // argon:CO2 mixture at 1 T: FP32 399 -> 372 ms, FP64 1004 -> 966 ms; waves of at most 16
-    // running lanes parking after half a device of secondaries: 379 and 988 ms; 48 lanes after
-    // a sixteenth: 384 and 960 ms).
-    const int64_t lanes = static_cast<int64_t>(dev.n_cu) * per_cu * o.block_size;
+    // records the queued secondaries unstarted (flag 8) and creates none.
+    //
+    // A generation by itself lasts as long as its longest electron, so a run with few electrons
+    // would spend most of its time on a few long chains, generation after generation.  While
+    // there are at most kSliceElectrons, a launch therefore runs its electrons only up to a
+    // common lineage count, parks them there, and the next launch resumes them together with the
+    // secondaries, which have caught up by its end.  (Ar:CO2 mixture at 1 T, ms with whole
+    // generations and with slices of 64, 128, 256 collisions: 500 primaries x 1500, FP32 18.0,
+    // 8.4, 10.0, 12.0, FP64 31.5, 13.7, 16.4, 20.6; 5000 x 1500, FP32 23.0, 16.2, 14.9, 17.4, FP64
+    // 38.9, 23.7, 25.0, 27.6; 20,000 x 800, FP32 11.6, 11.9, 10.6, 11.8; 100,000 x 2000, FP32, slices
+    // up to 100,000, 200,000 and 400,000 electrons: 71.0, 70.6, 81, 98.)
+    //
+    // Beyond that, a launch that has created secondaries for at least an eighth of the device's
+    // lanes lets its last few running electrons park (1e6 primaries: FP32 399 -> 372 ms, FP64
+    // 1004 -> 966 ms; waves of at most 16 running lanes parking after half a device of
+    // secondaries: 379 and 988 ms; 48 lanes after a sixteenth: 384 and 960 ms).
+    //
+    // No more than four waves per SIMD: the collisions of a magnetised mixture wait on L2, and the
+    // channel rows of more waves crowd it (100,000 primaries 73.3 ms with five, 70.4 with four, 72.0
+    // with three; 1e6 primaries x 1000 76.6 and 72.4 with five and four).
+    constexpr int64_t kSliceElectrons = 100'000;
+    const int groups_per_cu = std::max(1, std::min(per_cu, 16 * 64 / o.block_size));
+    const int64_t lanes = static_cast<int64_t>(dev.n_cu) * groups_per_cu * o.block_size;
     const int park_lanes = std::max(0, o.park_lanes);   // -1: never
-    const int64_t park_cap = parked_capacity(lanes, park_lanes);
-    if ((e = h->parked.ensure(2 * static_cast<size_t>(park_cap) * sizeof(ParkedState))) != hipSuccess)
-      return hip_fail(e, "allocating parked electrons");
+    // (where memory cannot hold the parked electrons of slices, those of a launch's end)
+    const int64_t end_cap = parked_capacity(lanes, park_lanes);
+    int64_t park_cap = park_lanes == 0 ? end_cap : std::max(end_cap, std::min(capacity, kSliceElectrons));
+    e = h->parked.ensure(2 * static_cast<size_t>(park_cap) * sizeof(ParkedState));
+    if (e == hipErrorOutOfMemory && park_cap > end_cap) {
+      (void)hipGetLastError();
+      park_cap = end_cap;
+      e = h->parked.ensure(2 * static_cast<size_t>(park_cap) * sizeof(ParkedState));
+    }
+    if (e != hipSuccess) return hip_fail(e, "allocating parked electrons");
     ParkedState* park_in = static_cast<ParkedState*>(h->parked.p);
     ParkedState* park_out = park_in + park_cap;
+    int64_t reached = 0;            // lineage count up to which every electron has run
     int64_t first = -1, count = n_electrons, queued = 0, n_parked = 0;
     h->n_launches = 0;
     h->n_parked = 0;
     for (;;) {
-      if ((e = launch_fill_u64(&d.ctr->gen_next, 0ull, 1, s)) != hipSuccess) return hip_fail(e, "generation counter");
-      if ((e = launch_fill_u64(&d.ctr->parked, 0ull, 1, s)) != hipSuccess) return hip_fail(e, "park counter");
-      const int64_t want = (n_parked + count + o.block_size - 1) / o.block_size;
-      const TeamShape team = may_team ? team_shape({n_parked + count}, {static_cast<double>(n_collisions)}, {d.trials}) : TeamShape{};
+      if ((e = launch_next_generation(d.ctr, s)) != hipSuccess) return hip_fail(e, "generation counters");
+      const int64_t electrons = n_parked + count;
+      const int64_t want = (electrons + o.block_size - 1) / o.block_size;
+      const TeamShape team = may_team ? team_shape({electrons}, {static_cast<double>(n_collisions)}, {d.trials}) : TeamShape{};
       // (the triggers of k_build_constants are for launches whose draining waves do not park)
       constexpr int kRealTrigger = 32;
       const int grid = team.lanes > 1
-          ? team_grid(team, (n_parked + count + team.per_group() - 1) / team.per_group())
-          : static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want * 4, static_cast<int64_t>(dev.n_cu) * per_cu)));
+          ? team_grid(team, (electrons + team.per_group() - 1) / team.per_group())
+          : static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want, static_cast<int64_t>(dev.n_cu) * groups_per_cu)));
+      const bool sliced = park_lanes > 0 && electrons <= std::min(park_cap, kSliceElectrons);
+      reached = sliced ? std::min(reached + (electrons <= 4000 ? 64 : 128), n_collisions) : n_collisions;
       const int64_t park_min = hc.dropped != 0 || park_lanes == 0 ? 0 : std::max<int64_t>(1, lanes / 8);
       if ((e = launch_swarm_real(h->d_desc, d.precision, h->has_b, trace, ext, o.block_size, grid,
                                  o.pending_trigger ? o.pending_trigger : kRealTrigger, lds,
                                  ch_off, ll.cum_off, first, count, hc.dropped != 0 ? 1 : 0, park_in, n_parked, park_out,
-                                 park_min, park_lanes, queued, s, team)) != hipSuccess)
+                                 park_min, park_lanes, queued, static_cast<uint32_t>(reached), park_cap, s, team)) != hipSuccess)
         return hip_fail(e, "swarm kernel launch");
       h->n_launches += 1;
       if ((e = hipMemcpyAsync(&hc, d.ctr, sizeof(hc), hipMemcpyDeviceToHost, s)) != hipSuccess) return hip_fail(e, "counters");
@@ -895,8 +921,7 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
       first = queued;
       count = tail - queued;
       queued = tail;
-      n_parked = std::min<int64_t>(static_cast<int64_t>(hc.parked),
-                                   parked_capacity(static_cast<int64_t>(grid) * (team.lanes > 1 ? team.block : o.block_size), park_lanes));
+      n_parked = std::min<int64_t>(static_cast<int64_t>(hc.parked), park_cap);
       h->n_parked += n_parked;
       std::swap(park_in, park_out);
     }

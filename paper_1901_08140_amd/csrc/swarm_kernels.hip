@@ -565,6 +565,11 @@ __global__ void k_fill_u64(uint64_t* p, uint64_t v, int64_t n) {
     p[i] = v;
 }
 
+__global__ void k_next_generation(RunCounters* ctr) {
+  ctr->gen_next = 0;
+  ctr->parked = 0;
+}
+
 // =======================================================================================
 // Per-electron null-collision loop.
 // =======================================================================================
@@ -2399,13 +2404,14 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
 // atomic and hands them to its idle lanes by ballot rank, and it reads the overflow
 // counter once every 64 passes, so no pass waits on device-coherent memory.  With `flush`
 // set (the launch after an overflow) every electron is recorded as it was created.
-// A launch also resumes the electrons the launch before it parked (park_in, taken first).
-// Once all of its electrons are claimed, a wave that is down to park_lanes running lanes or
-// fewer, in a launch that has created at least park_min secondaries so far, parks them: each lane
-// stops at its next real collision and writes its resumable state to park_out, and the
-// next launch runs them together with those secondaries instead of this launch idling
-// through their tail.  Parking moves no electron to another stream position, so the
-// results do not depend on it.
+// A launch also resumes the electrons the launch before it parked (park_in, taken first).  A
+// lane whose electron reaches k_limit before its budget's end writes its resumable state to
+// park_out and takes another one.  Once all of the launch's electrons are claimed, a wave that
+// is down to park_lanes running lanes or fewer, in a launch that has created at least park_min
+// secondaries so far, parks them too: each lane stops at its next real collision, and the next
+// launch runs them together with those secondaries instead of this launch idling through
+// their tail.  Parking moves no electron to another stream position, so the results do not
+// depend on it.
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t kClaimChunk = 64;      // electrons a wave takes per claim
 constexpr uint32_t kAbortPoll = 64;       // passes between reads of the overflow counter
@@ -2417,7 +2423,8 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
                                                     int flush, const ParkedState* __restrict__ park_in,
                                                     int64_t n_park_in, ParkedState* __restrict__ park_out,
                                                     int64_t park_min, int park_lanes, int64_t tail0,
-                                                    int g, int per_wave, uint32_t scarce) {
+                                                    int g, int per_wave, uint32_t scarce, uint32_t k_limit,
+                                                    uint32_t park_cap) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
@@ -2467,12 +2474,12 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
           const ParkedState ps = park_in[e];
           load_saved<R, HB, EXT>(ps.s, L, C);
           L.rec = ps.rec;
-          L.k_stop = C.n_coll;
+          L.k_stop = k_limit;
           L.state = ST_ACTIVE;
         } else if (first < 0) {
           init_primary<R, HB, EXT>(L, C, s_nu, e - n_park_in);
           L.rec = static_cast<int64_t>(e - n_park_in);
-          L.k_stop = C.n_coll;
+          L.k_stop = k_limit;
           L.state = ST_ACTIVE;
         } else {
           const int64_t slot = first + static_cast<int64_t>(e - n_park_in);
@@ -2482,7 +2489,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
           L.vx = static_cast<R>(cs.v[0]); L.vy = static_cast<R>(cs.v[1]); L.vz = static_cast<R>(cs.v[2]);
           set_id(L, C, cs.id);
           L.k = L.k_start = cs.k;
-          L.k_stop = C.n_coll;
+          L.k_stop = k_limit;
           L.block = 0;
           L.G = L.D = L.nforb = L.nover = L.nfirst = L.flags = 0;
           L.se = L.sep = 0.0;
@@ -2491,7 +2498,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
           set_anchor<R, HB>(L, C);
           start_trial_frequency<R, EXT>(L, C, s_nu, static_cast<R>(cs.eps_birth));
           // a secondary born at its lineage's last collision has nothing left to do
-          L.state = L.k >= L.k_stop ? ST_STOPPED : ST_ACTIVE;
+          L.state = L.k >= C.n_coll ? ST_STOPPED : ST_ACTIVE;
         }
         // after an overflow, electrons not yet started are recorded as they are (flag 8)
         if (L.state == ST_ACTIVE && aborting) {
@@ -2564,21 +2571,20 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
       L.state = ST_STOPPED;
     }
     if (L.state == ST_STOPPED) {
-      if (parking && L.k < C.n_coll && !(L.flags & 14u)) {
-        // parked (not attached, capped or aborted): resumed by the next launch.  The slots
-        // stay below parked_capacity of the launch's threads, which the host's buffers hold;
-        // past that a lane would run on.
+      if (L.k < C.n_coll && !(L.flags & 14u)) {
+        // parked (not attached, capped or aborted): resumed by the next launch.  Past the host's
+        // buffers a lane runs on.
         unsigned long long ps = 0;
         if (!TEAM || team.sub == 0) ps = atomicAdd(reinterpret_cast<unsigned long long*>(&ctr->parked), 1ull);
         if constexpr (TEAM) ps = __shfl(ps, team.base);
-        if (ps < static_cast<uint64_t>(parked_capacity(static_cast<int64_t>(gridDim.x) * blockDim.x, park_lanes))) {
+        if (ps < park_cap) {
           if (!TEAM || team.sub == 0) {
             ParkedState p;
             p.s = saved_of<R, EXT>(L, C);
             p.rec = L.rec;
             park_out[ps] = p;
           }
-          L.state = ST_DONE;
+          L.state = ST_IDLE;
         } else {
           L.k_stop = C.n_coll;
           set_anchor<R, HB>(L, C);
@@ -2896,6 +2902,11 @@ hipError_t launch_fill_u64(uint64_t* p, uint64_t v, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t launch_next_generation(RunCounters* ctr, hipStream_t s) {
+  hipLaunchKernelGGL(k_next_generation, dim3(1), dim3(1), 0, s, ctr);
+  return hipGetLastError();
+}
+
 size_t swarm_pool_slot_bytes(int precision) {
   const size_t r = precision == SWARM_FP32_MIXED ? sizeof(float) : sizeof(double);
   return kPoolD * sizeof(double) + kPoolR * r + kPoolU * sizeof(uint32_t);
@@ -2928,17 +2939,19 @@ hipError_t launch_swarm_real(const InstanceDesc* d_desc, int precision, bool has
                              int ext, int block_size, int grid, int pending_trigger, size_t lds_bytes,
                              int ch_off, int cum_off, int64_t first, int64_t count, int flush,
                              const ParkedState* park_in, int64_t n_park_in, ParkedState* park_out,
-                             int64_t park_min, int park_lanes, int64_t tail0, hipStream_t s, TeamShape team) {
+                             int64_t park_min, int park_lanes, int64_t tail0, uint32_t k_limit, int64_t park_cap, hipStream_t s,
+                             TeamShape team) {
   const bool teams = team.lanes > 1 && !trace;
   void* fn = teams ? pick_team(precision, has_b, ext, true) : pick_kernel(precision, has_b, trace, true, ext);
   if (teams) {
     block_size = team.block;
     pending_trigger = team.trigger;
   }
+  uint32_t cap = static_cast<uint32_t>(std::min<int64_t>(park_cap, 0xffffffffLL));
   uint32_t scarce = 2u * (teams ? static_cast<uint32_t>(team.per_wave) : kClaimChunk) * static_cast<uint32_t>(grid * (block_size / 64));
   void* args[] = {const_cast<InstanceDesc**>(&d_desc), &pending_trigger, &ch_off, &cum_off, &first, &count, &flush,
                   const_cast<ParkedState**>(&park_in), &n_park_in, &park_out, &park_min, &park_lanes, &tail0,
-                  &team.lanes, &team.per_wave, &scarce};
+                  &team.lanes, &team.per_wave, &scarce, &k_limit, &cap};
   return hipLaunchKernel(fn, dim3(grid), dim3(block_size), args, lds_bytes, s);
 }
 

@@ -56,16 +56,20 @@ def test_team_relativistic_and_anisotropic(gpu):
 
 @pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "fp32"])
 def test_team_lineages_equal_one_lane_lineages(gpu, precision):
-    """Real secondaries, with and without parking, and a capacity that overflows."""
+    """Real secondaries: in slices of the lineage budget with eager and default parking, in whole
+    generations (no parking), budgets around a slice's end, and a capacity that overflows."""
     cfg = synth.cfg3_mixture_real()
-    for n_e, n_c, park in ((3, 900, 0), (700, 900, 64), (700, 900, -1)):
-        out = []
-        for shape in ({"park_lanes": park}, {"park_lanes": park, **ONE_LANE}):
+    for n_e, n_c in ((3, 900), (700, 900), (40, 63), (40, 64), (40, 65), (4100, 130)):
+        ref = None
+        for shape in ({"park_lanes": -1, **ONE_LANE}, {"park_lanes": -1}, {}, ONE_LANE, {"park_lanes": 64}):
             s = gpu.Swarm.from_config(cfg, precision)
             s.set_launch_opts(shape)
             s.run(n_e, n_c, 5)
-            out.append(sort_by_id(s.records()))
-        assert out[0].tobytes() == out[1].tobytes(), (n_e, park)
+            got = sort_by_id(s.records())
+            if ref is None:
+                ref = got
+                assert s.launches()[1] == 0
+            assert got.tobytes() == ref.tobytes(), (n_e, n_c, shape)
     s = gpu.Swarm.from_config(cfg, precision, capacity=800)
     with pytest.raises(gpu.SwarmError) as err:
         s.run(700, 2000, 5)
