@@ -1023,6 +1023,18 @@ swarm_status swarm_records(swarm_t h, swarm_record* out, int64_t max_records, in
   if (h->in_flight) return busy();
   if (h->noalloc_records) return fail(SWARM_ERR_STATE, "the last run wrote its records to caller memory");
   if (!h->have_run) return fail(SWARM_ERR_STATE, "no completed run");
+  // A complete run has a record in every slot: counted without a copy, and copied straight to the
+  // caller (through a vector and twice, to count first, the 100,000 records of an FP64 point
+  // took 2.6-6.6 ms beside 10 ms of simulation; straight, 1.2-3.0).
+  if (h->run_status == SWARM_OK) {
+    *n_out = h->n_records;
+    const int64_t n = std::min(h->n_records, max_records);
+    if (!out || n <= 0) return SWARM_OK;
+    hipError_t e = hipMemcpyAsync(out, h->desc.records, static_cast<size_t>(n) * sizeof(swarm_record),
+                                  hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    return e == hipSuccess ? SWARM_OK : hip_fail(e, "copying records");
+  }
   // Slots of secondaries that a run stopped early never simulated are empty (id all ones)
   // and are left out: *n_out counts the electrons that have a record.
   std::vector<swarm_record> all(static_cast<size_t>(h->n_records));
