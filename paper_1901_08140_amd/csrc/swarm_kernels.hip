@@ -112,6 +112,10 @@ __device__ __forceinline__ double uni(uint32_t hi, uint32_t lo, double) {
 __device__ __forceinline__ float uni(uint32_t hi, uint32_t, float) {
   return static_cast<float>(hi >> 8) * 0x1.0p-24f;
 }
+// The FP64 uniform times 2^53, an integer below 2^53.
+__device__ __forceinline__ double uni53(uint32_t hi, uint32_t lo) {
+  return fma(static_cast<double>(hi), 0x1.0p21, static_cast<double>(lo >> 11));
+}
 // 1 - u for the FP64 uniform of (hi, lo), formed directly: 1 - lo' 2^-53 and then minus
 // hi 2^-32 are both exact, so this equals 1 - uni(hi, lo) bit for bit, one step shorter.
 __device__ __forceinline__ double one_minus_uni(uint32_t hi, uint32_t lo) {
@@ -119,8 +123,11 @@ __device__ __forceinline__ double one_minus_uni(uint32_t hi, uint32_t lo) {
 }
 
 // Flight-time increment -ln(1-u)/nu' (eq. random_time) in FP64, cT = 1/nu': 1-u is exact,
-// and its logarithm comes from the table-driven unit_log (about 20 instructions where the
-// library logarithm takes about 85), with the table staged in LDS.  The FP32 trial forms
+// and its logarithm comes from the table-driven unit_log (about 27 instructions where the
+// library logarithm takes about 85), with the table staged in LDS.  (Its shorter form, the
+// integer times nu' 2^-53 and the median-of-three index took a trial from 63 to 50
+// instructions after its random words: an argon sweep of 32 x 1e5 x 2000 250 -> 239 ms, one
+// point of it 9.62 -> 9.36 ms, 1e5 x 1000 of a magnetised mixture 8.6 -> 8.4 ms.)  The FP32 trial forms
 // its own from the 24-bit word (one_trial).
 __device__ __forceinline__ double flight(double one_minus_u, double cT, const double* __restrict__ logtab) {
   return -unit_log(one_minus_u, logtab) * cT;
@@ -581,7 +588,7 @@ struct Consts {
   R omega_rev;   // omega / (2 pi): the gyration phase in revolutions
   R inv_omega;   // 1 / omega (B > 0), divided once per work item instead of per collision
   R aze, apare;  // accelerations in energy units (FP32: times sqrt(m/2e); FP64: plain)
-  R nup24;       // FP32: nu' 2^-24 (x = R nu' straight from the 24-bit integer)
+  R nup24;       // FP32: nu' 2^-24, FP64: nu' 2^-53 (x = R nu' straight from the integer)
   R Pf, twoPf;   // grid points per octave, and twice that, as floating point
   R sceps;       // FP32: sqrt(m/2e)
   R zeta1;       // variable trial frequency: 1 + zeta
@@ -597,6 +604,7 @@ struct Consts {
   int G, nc, off, p;
   int off1;      // off - 1: raw index of entry 0 of the padded LDS table
   int off1G;     // off1 + G: raw index of its last entry
+  int off1G_v;   // FP64: the same in a vector register, see load_consts
   float e_lo, e_hi;   // FP32: the float just below 2^emin, and 2^emax (the clamp of the index;
                       // e_hi is held in a vector register, see load_consts)
   uint32_t wmask;     // FP32: the low 23-p mantissa bits (the interpolation weight, unscaled)
@@ -628,7 +636,7 @@ __device__ __forceinline__ Consts<R> load_consts(const InstanceDesc& d) {
     c.off = (127 + d.emin) << d.p_log2;
   }
   if constexpr (sizeof(R) == 8) {
-    c.aze = d.az; c.apare = d.apar; c.nup24 = 0.0; c.sceps = 1.0;
+    c.aze = d.az; c.apare = d.apar; c.nup24 = d.majorant * 0x1.0p-53; c.sceps = 1.0;
     c.Pf = d.Pf_d; c.twoPf = d.twoPf_d;
   } else {
     c.aze = d.aze_f; c.apare = d.apare_f; c.nup24 = d.nup24_f; c.sceps = d.sceps_f;
@@ -663,6 +671,7 @@ __device__ __forceinline__ Consts<R> load_consts(const InstanceDesc& d) {
   // work item instead of a move in every trial.
   const float e_hi = __uint_as_float(static_cast<uint32_t>(127 + d.emax) << 23);
   asm("v_mov_b32 %0, %1" : "=v"(c.e_hi) : "s"(e_hi));
+  asm("v_mov_b32 %0, %1" : "=v"(c.off1G_v) : "s"(c.off1G));
   return c;
 }
 
@@ -920,7 +929,8 @@ __device__ __forceinline__ R energy_at(const Lane<R>& L, const Consts<R>& C, R T
 // 0, as below the grid.  With MED3 the FP32 trial clamps the energy instead, to [the float
 // below 2^emin, 2^emax], whose indices are off1 and off1 + G: one median-of-three instead of
 // a maximum and a minimum, for a vector register that holds the upper bound (taken where the
-// kernel has one to spare: B = 0 with the constant trial frequency).
+// kernel has one to spare: B = 0 with the constant trial frequency).  FP64 takes the median of
+// the indices themselves (of energies it would take two instructions).
 template <bool MED3 = false>
 __device__ __forceinline__ int raw_index(float eps, const Consts<float>& C) {
   if constexpr (MED3)
@@ -930,8 +940,14 @@ __device__ __forceinline__ int raw_index(float eps, const Consts<float>& C) {
 }
 template <bool MED3 = false>
 __device__ __forceinline__ int raw_index(double eps, const Consts<double>& C) {
-  const int32_t hi = static_cast<int32_t>(static_cast<uint64_t>(__double_as_longlong(eps)) >> 32);
-  return min(max(hi >> (20 - C.p), C.off1), C.off1G);    // arithmetic shift: negative -> entry 0
+  const int32_t raw = __double2hiint(eps) >> (20 - C.p);    // arithmetic shift: negative -> entry 0
+  if constexpr (MED3) {
+    int r;      // off1 <= off1G
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(raw), "s"(C.off1), "v"(C.off1G_v));
+    return r;
+  } else {
+    return min(max(raw, C.off1), C.off1G);
+  }
 }
 template <bool MED3 = false>
 __device__ __forceinline__ float lds_rate(const float2* __restrict__ s_nu, float eps, const Consts<float>& C,
@@ -946,7 +962,7 @@ __device__ __forceinline__ float lds_rate(const float2* __restrict__ s_nu, float
 template <bool MED3 = false>
 __device__ __forceinline__ double lds_rate(const double2* __restrict__ s_nu, double eps, const Consts<double>& C,
                                           int* raw_out, double* w_out) {
-  const int raw = raw_index(eps, C);
+  const int raw = raw_index<MED3>(eps, C);
   const double w = __builtin_amdgcn_fract(__builtin_amdgcn_frexp_mant(eps) * C.twoPf);
   const double2 q = (s_nu - C.off1)[raw];
   *raw_out = raw;
@@ -1266,7 +1282,7 @@ __device__ __forceinline__ bool one_trial(Lane<R>& L, const Consts<R>& C,
     L.p_x = static_cast<float>(hr >> 8) * (EXT ? L.nup24 : C.nup24);    // = u_r nu' exactly
   } else {
     L.T = L.T + flight(one_minus_uni(hf, lf), EXT ? L.cT : C.cT, C.logtab);
-    L.p_x = uni(hr, lr, R(0)) * (EXT ? L.nup : C.nup);
+    L.p_x = EXT ? uni(hr, lr, R(0)) * L.nup : uni53(hr, lr) * C.nup24;
   }
   L.p_eps = energy_at<R, HB, EXT>(L, C, L.T);
   const R nu = lds_rate<!HB && EXT == 0>(s_nu, L.p_eps, C, &L.p_gi, &L.p_w);
@@ -1876,7 +1892,7 @@ __global__ void __launch_bounds__(512, (dummy_waves<R, HB, TR, EXT>())) k_swarm_
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
-  __shared__ double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
+  __shared__ __align__(16) double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
   __shared__ unsigned long long s_best;
   int inst = plan.first != nullptr ? __builtin_amdgcn_readfirstlane(plan.first[blockIdx.x]) : 0;
@@ -1983,7 +1999,7 @@ __device__ __forceinline__ TrialPoint<R> trial_point(const Lane<R>& L, const Con
   TrialPoint<R> t;
   t.T = T;
   if constexpr (sizeof(R) == 4) t.x = static_cast<float>(hr >> 8) * (EXT ? L.nup24 : C.nup24);
-  else t.x = uni(hr, lr, R(0)) * (EXT ? L.nup : C.nup);
+  else t.x = EXT ? uni(hr, lr, R(0)) * L.nup : uni53(hr, lr) * C.nup24;
   t.eps = energy_at<R, HB, EXT>(L, C, T);
   const R nu = lds_rate<!HB && EXT == 0>(s_nu, t.eps, C, &t.gi, &t.w);
   t.hit = t.x < nu;
@@ -2058,7 +2074,7 @@ __global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restri
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
-  __shared__ double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
+  __shared__ __align__(16) double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
   __shared__ unsigned long long s_best;
   const int lane = static_cast<int>(threadIdx.x) & 63;
@@ -2272,7 +2288,7 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
-  __shared__ double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
+  __shared__ __align__(16) double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
   __shared__ unsigned long long s_best;
   __shared__ int s_ncand[2];   // pool slots asked for, by round parity
@@ -2428,7 +2444,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
-  __shared__ double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
+  __shared__ __align__(16) double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
   const InstanceDesc& d = *desc;
   stage_instance<R>(d, smem, s_ch, s_logtab, cum_off);
