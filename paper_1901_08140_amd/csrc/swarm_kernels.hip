@@ -266,7 +266,7 @@ __device__ __forceinline__ double lerp_pair(double2 q, double w) { return q.x + 
 // =======================================================================================
 // Table build (create time): raw tables -> extension -> rates on the octave grid ->
 // running sums over channels -> pairs for the kernels; then the trial frequency and the
-// field constants.  One thread per grid node.
+// field constants.
 // =======================================================================================
 
 // Cross-section of raw channel c at eps with the extension rules of section "Extension of
@@ -309,30 +309,67 @@ __device__ double sigma_ext(const InstanceDesc& d, int c, double eps) {
   return s[lo - 1] + (s[lo] - s[lo - 1]) * t;
 }
 
+__device__ __forceinline__ double node_energy(const InstanceDesc& d, int g) {
+  const int P = 1 << d.p_log2;
+  return ldexp(1.0 + static_cast<double>(g % P) / P, d.emin + g / P);
+}
+
+// The rate of every channel at every node, one thread each.  Each thread waits for a chain of
+// table reads (the binary search) and logarithms, so it is the longest chain that counts: with
+// one thread per node and a loop over its channels the rates and sums took 25 us for 5
+// channels, 115 for 28 and 62 to 414 for random gases of up to a hundred; now 15, 20 and 14 to 29.
 __global__ void k_build_rates(InstanceDesc* desc) {
   const InstanceDesc& d = *desc;
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
+  const int per_channel = (d.G + static_cast<int>(blockDim.x) - 1) / static_cast<int>(blockDim.x);
+  const int c = static_cast<int>(blockIdx.x) / per_channel;
+  const int g = static_cast<int>(blockIdx.x) % per_channel * static_cast<int>(blockDim.x) + static_cast<int>(threadIdx.x);
   if (g >= d.G) return;
-  const int P = 1 << d.p_log2;
-  const int o = g / P, i = g % P;
-  const double eps = ldexp(1.0 + static_cast<double>(i) / P, d.emin + o);
+  const double eps = node_energy(d, g);
   const double ej = eps * kQe;
   const double speed = d.relativistic ? sqrt(2.0 * ej / kMe * (1.0 + ej / (2.0 * kMe * kC * kC))) / (1.0 + ej / (kMe * kC * kC))
                                       : sqrt(2.0 * ej / kMe);
+  // eq. frequency: nu_c = n_k sigma_c(eps) v, eps in joule, v = sqrt(2 eps / m); the
+  // relativistic mover takes the true speed |u|/gamma, |u| = sqrt(2 eps/m (1 + eps/(2 m c^2)))
+  // the proper speed and gamma = 1 + eps/(m c^2)
+  const double dens = d.comp_frac[d.raw_comp[c]] * d.N;
+  d.cum_cm[static_cast<size_t>(c) * d.G + g] = dens * sigma_ext(d, c, eps) * speed;
+}
+
+// Running sums over the channels of every node, in place and in channel order.  The loss of
+// every channel, a + b eps, is prepared by one lane each for all the nodes of the wave.
+__global__ void __launch_bounds__(64) k_build_sums(InstanceDesc* desc) {
+  const InstanceDesc& d = *desc;
+  __shared__ double s_a[64], s_b[64];
+  const int node = blockIdx.x * 64 + threadIdx.x;
+  const int g = min(node, d.G - 1);           // (past the grid: the top node's values, not written)
+  const double eps = node_energy(d, g);
+  double* nu = d.cum_cm + g;
   double acc = 0.0, loss = 0.0;
-  for (int c = 0; c < d.nc; ++c) {
-    const int comp = d.raw_comp[c];
-    const double before = acc;
-    const double dens = d.comp_frac[comp] * d.N;
-    // eq. frequency: nu_c = n_k sigma_c(eps) v, eps in joule, v = sqrt(2 eps / m); the
-    // relativistic mover takes the true speed |u|/gamma, |u| = sqrt(2 eps/m (1 + eps/(2 m c^2)))
-    // the proper speed and gamma = 1 + eps/(m c^2)
-    acc += dens * sigma_ext(d, c, eps) * speed;
-    d.cum_cm[static_cast<size_t>(c) * d.G + g] = acc;
-    const double lost = d.raw_kind[c] == SWARM_ATTACHMENT ? eps
-                      : (d.raw_kind[c] == SWARM_ELASTIC ? 0.0 : d.raw_thr[c]) + 2.0 * kMe / (d.comp_mass_amu[comp] * kAmu) * eps;
-    loss += (acc - before) * lost;
+  constexpr int kAtOnce = 8;            // rates read ahead of their sums
+  for (int c0 = 0; c0 < d.nc; c0 += 64) {
+    const int n = min(d.nc - c0, 64);
+    __syncthreads();
+    if (static_cast<int>(threadIdx.x) < n) {
+      const int c = c0 + threadIdx.x, kind = d.raw_kind[c];
+      s_a[threadIdx.x] = kind == SWARM_ATTACHMENT || kind == SWARM_ELASTIC ? 0.0 : d.raw_thr[c];
+      s_b[threadIdx.x] = kind == SWARM_ATTACHMENT ? 1.0 : 2.0 * kMe / (d.comp_mass_amu[d.raw_comp[c]] * kAmu);
+    }
+    __syncthreads();
+    for (int i0 = 0; i0 < n; i0 += kAtOnce) {
+      double r[kAtOnce];
+#pragma unroll
+      for (int i = 0; i < kAtOnce; ++i) r[i] = nu[static_cast<size_t>(c0 + min(i0 + i, n - 1)) * d.G];
+#pragma unroll
+      for (int i = 0; i < kAtOnce; ++i) {
+        if (i0 + i >= n) break;
+        const double before = acc;
+        acc += r[i];
+        if (node < d.G) nu[static_cast<size_t>(c0 + i0 + i) * d.G] = acc;
+        loss += (acc - before) * (s_a[i0 + i] + s_b[i0 + i] * eps);
+      }
+    }
   }
+  if (node >= d.G) return;
   d.nodes[g] = eps;
   // Energy balance (eV/s): the heating of an electron that collides at the rate acc, along B
   // and across it, against its mean loss in collisions.  Electrons live around the lowest
@@ -425,6 +462,21 @@ __global__ void k_build_constants(InstanceDesc* desc) {
     th.cM = M / (mm + M);
     d.chan_th[c] = th;
   }
+  // Candidates of c_speed_f (below), one per thread: consecutive floats from 16 below the
+  // rounded constant to 16 above.
+  constexpr int kSpeeds = 33;
+  __shared__ double s_misfit[kSpeeds];
+  const double c_speed = sqrt(2.0 * kQe / kMe);
+  const uint32_t cs_bits = __float_as_uint(static_cast<float>(c_speed)) - 16u;
+  if (threadIdx.x < kSpeeds) {
+    const double c = static_cast<double>(__uint_as_float(cs_bits + threadIdx.x));
+    const float sc = static_cast<float>(1.0 / c);
+    const float ce = static_cast<float>(1.0 / (c * c));
+    const double r1 = fabs(static_cast<double>(ce) * c * c - 1.0);
+    const double r2 = fabs(static_cast<double>(sc) * static_cast<double>(sc) * c * c - 1.0);
+    s_misfit[threadIdx.x] = fmax(r1, r2);
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
     const double numax = smax[0];
     d.numax = numax;
@@ -453,7 +505,7 @@ __global__ void k_build_constants(InstanceDesc* desc) {
     d.majorant_f = static_cast<float>(nup);
     d.cT_f = static_cast<float>(kLn2 / nup);
     d.c_eps = 0.5 * kMe / kQe;
-    d.c_speed = sqrt(2.0 * kQe / kMe);
+    d.c_speed = c_speed;
     // (relativistic mover: the proper speed gamma |v|)
     d.speed0 = sqrt(2.0 * d.eps0 * kQe / kMe * (d.relativistic ? 1.0 + d.eps0 * kQe / (2.0 * kMe * kC * kC) : 1.0));
     d.az = -kQe * d.E / kMe;
@@ -495,20 +547,12 @@ __global__ void k_build_constants(InstanceDesc* desc) {
     // mean-energy bias of 1e-7 M/(2m).  c_speed is moved by at most 16 units in the last place
     // so that c_eps c_speed^2 and (sceps c_speed)^2 both equal 1 to about 1e-8.
     {
-      const float base = static_cast<float>(d.c_speed);
-      float best_cs = base, best_sc = static_cast<float>(sqrt(d.c_eps)), best_ce = static_cast<float>(d.c_eps);
-      double best_r = 1e300;
-      float cs = base;
-      for (int i = 0; i < 16; ++i) cs = nextafterf(cs, 0.0f);
-      for (int i = 0; i <= 32; ++i, cs = nextafterf(cs, 1e30f)) {
-        const double c = static_cast<double>(cs);
-        const float sc = static_cast<float>(1.0 / c);
-        const float ce = static_cast<float>(1.0 / (c * c));
-        const double r1 = fabs(static_cast<double>(ce) * c * c - 1.0);
-        const double r2 = fabs(static_cast<double>(sc) * static_cast<double>(sc) * c * c - 1.0);
-        const double r = fmax(r1, r2);
-        if (r < best_r) { best_r = r; best_cs = cs; best_sc = sc; best_ce = ce; }
-      }
+      int best = 0;
+      for (int i = 1; i < kSpeeds; ++i)
+        if (s_misfit[i] < s_misfit[best]) best = i;
+      const float best_cs = __uint_as_float(cs_bits + static_cast<uint32_t>(best));
+      const double c = static_cast<double>(best_cs);
+      const float best_sc = static_cast<float>(1.0 / c), best_ce = static_cast<float>(1.0 / (c * c));
       d.c_speed_f = best_cs;
       d.c_eps_f = best_ce;
       d.sceps_f = best_sc;
@@ -2889,7 +2933,8 @@ void* pick_kernel(int precision, bool has_b, bool trace, bool real, int ext) {
 // Host-side launchers.
 // =======================================================================================
 hipError_t launch_build(InstanceDesc* d_desc, const InstanceDesc& h, hipStream_t s) {
-  hipLaunchKernelGGL(k_build_rates, dim3((h.G + 127) / 128), dim3(128), 0, s, d_desc);
+  hipLaunchKernelGGL(k_build_rates, dim3((h.G + 127) / 128 * h.nc), dim3(128), 0, s, d_desc);
+  hipLaunchKernelGGL(k_build_sums, dim3((h.G + 63) / 64), dim3(64), 0, s, d_desc);
   const int64_t n = static_cast<int64_t>(h.G) * h.nc;
   hipLaunchKernelGGL(k_build_pairs, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, d_desc);
   hipLaunchKernelGGL(k_build_constants, dim3(1), dim3(256), 0, s, d_desc);
