@@ -95,7 +95,9 @@ struct RunCounters {
   uint64_t dropped;       // secondaries that did not fit the capacity
   uint64_t n_done;        // dummy mode: electrons that reached their final collision or stopped
   uint64_t parked;        // real mode: electrons the running launch parked for the next one
-  uint64_t pad2[13];
+  uint32_t k_min;         // real mode: smallest lineage count it left to the next launch
+  uint32_t pad2;
+  uint64_t pad3[12];
 };
 
 // One swarm instance as seen by the kernels.  Fields in the first group are written by
@@ -224,8 +226,9 @@ hipError_t launch_swarm_dummy(const InstanceDesc* d_desc, ClaimPlan plan, int pr
 size_t swarm_pool_slot_bytes(int precision);
 // One real-secondaries launch: the n_park_in electrons in park_in (parked by the launch
 // before), then `count` electrons from `first` (the primaries if first < 0, else queued
-// secondaries).  An electron whose lineage count reaches k_limit before its budget's end is
-// parked in park_out (park_cap slots; past them it runs on).  Once every electron is claimed, a
+// secondaries).  An electron whose lineage count reaches k_limit, or slice collisions more than
+// it starts with if that is later, before its budget's end is parked in park_out (park_cap
+// slots; past them it runs on).  Once every electron is claimed, a
 // wave left with few running lanes parks them too, at their next real-collision boundary,
 // provided this launch has created at least park_min secondaries (the queue started at tail0);
 // park_lanes is the most running lanes such a wave may have, and park_min <= 0 parks none this
@@ -234,9 +237,9 @@ hipError_t launch_swarm_real(const InstanceDesc* d_desc, int precision, bool has
                              int ext, int block_size, int grid, int pending_trigger, size_t lds_bytes,
                              int ch_off, int cum_off, int64_t first, int64_t count, int flush,
                              const ParkedState* park_in, int64_t n_park_in, ParkedState* park_out,
-                             int64_t park_min, int park_lanes, int64_t tail0, uint32_t k_limit, int64_t park_cap, hipStream_t s,
+                             int64_t park_min, int park_lanes, int64_t tail0, uint32_t k_limit, uint32_t slice, int64_t park_cap, hipStream_t s,
                              TeamShape team);
-// Clears the counters of a real-secondaries launch (electrons taken, electrons parked).
+// Resets the counters of a real-secondaries launch (electrons taken and parked, smallest count).
 hipError_t launch_next_generation(RunCounters* ctr, hipStream_t s);
 hipError_t launch_tallies(const InstanceDesc* d_desc, const TallyTile* d_tiles, int32_t n_tiles,
                           const int32_t* d_tile_base, const int64_t* d_nrec, int32_t n_inst,

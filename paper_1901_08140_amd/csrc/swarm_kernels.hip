@@ -619,6 +619,7 @@ __global__ void k_fill_u64(uint64_t* p, uint64_t v, int64_t n) {
 __global__ void k_next_generation(RunCounters* ctr) {
   ctr->gen_next = 0;
   ctr->parked = 0;
+  ctr->k_min = ~0u;
 }
 
 // =======================================================================================
@@ -2465,8 +2466,8 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
 // counter once every 64 passes, so no pass waits on device-coherent memory.  With `flush`
 // set (the launch after an overflow) every electron is recorded as it was created.
 // A launch also resumes the electrons the launch before it parked (park_in, taken first).  A
-// lane whose electron reaches k_limit before its budget's end writes its resumable state to
-// park_out and takes another one.  Once all of the launch's electrons are claimed, a wave that
+// lane whose electron reaches its stop (k_limit, or slice collisions after its start) before its
+// budget's end writes its resumable state to park_out and takes another one.  Once all of the launch's electrons are claimed, a wave that
 // is down to park_lanes running lanes or fewer, in a launch that has created at least park_min
 // secondaries so far, parks them too: each lane stops at its next real collision, and the next
 // launch runs them together with those secondaries instead of this launch idling through
@@ -2484,7 +2485,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
                                                     int64_t n_park_in, ParkedState* __restrict__ park_out,
                                                     int64_t park_min, int park_lanes, int64_t tail0,
                                                     int g, int per_wave, uint32_t scarce, uint32_t k_limit,
-                                                    uint32_t park_cap) {
+                                                    uint32_t slice, uint32_t park_cap) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
@@ -2520,6 +2521,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
   WaveClaim claims;
   bool aborting = flush != 0, parking = false;
   uint32_t pass = 0;
+  uint32_t k_min = ~0u;       // of the electrons this lane leaves to the next launch
   for (;;) {
     const uint64_t idle = __ballot(L.state == ST_IDLE);
     if (idle != 0) {
@@ -2534,12 +2536,10 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
           const ParkedState ps = park_in[e];
           load_saved<R, HB, EXT>(ps.s, L, C);
           L.rec = ps.rec;
-          L.k_stop = k_limit;
           L.state = ST_ACTIVE;
         } else if (first < 0) {
           init_primary<R, HB, EXT>(L, C, s_nu, e - n_park_in);
           L.rec = static_cast<int64_t>(e - n_park_in);
-          L.k_stop = k_limit;
           L.state = ST_ACTIVE;
         } else {
           const int64_t slot = first + static_cast<int64_t>(e - n_park_in);
@@ -2549,7 +2549,6 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
           L.vx = static_cast<R>(cs.v[0]); L.vy = static_cast<R>(cs.v[1]); L.vz = static_cast<R>(cs.v[2]);
           set_id(L, C, cs.id);
           L.k = L.k_start = cs.k;
-          L.k_stop = k_limit;
           L.block = 0;
           L.G = L.D = L.nforb = L.nover = L.nfirst = L.flags = 0;
           L.se = L.sep = 0.0;
@@ -2560,6 +2559,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
           // a secondary born at its lineage's last collision has nothing left to do
           L.state = L.k >= C.n_coll ? ST_STOPPED : ST_ACTIVE;
         }
+        L.k_stop = min(C.n_coll, max(k_limit, L.k + slice));
         // after an overflow, electrons not yet started are recorded as they are (flag 8)
         if (L.state == ST_ACTIVE && aborting) {
           L.flags |= 8u;
@@ -2615,6 +2615,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
         base = __shfl(base, leader);
         if (spawn) {
           const int64_t s = static_cast<int64_t>(base + __popcll(sm & lane_lt));
+          k_min = min(k_min, L.k);
           if (s < child_cap) d.children[s] = make_child<R, EXT>(L, C);
           else atomicAdd(reinterpret_cast<unsigned long long*>(&ctr->dropped), 1ull);
         }
@@ -2644,6 +2645,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
             p.rec = L.rec;
             park_out[ps] = p;
           }
+          k_min = min(k_min, L.k);
           L.state = ST_IDLE;
         } else {
           L.k_stop = C.n_coll;
@@ -2658,6 +2660,8 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
     }
     if (__ballot(L.state != ST_DONE) == 0) break;
   }
+  for (int s = 32; s > 0; s >>= 1) k_min = min(k_min, static_cast<uint32_t>(__shfl_xor(static_cast<int>(k_min), s)));
+  if ((threadIdx.x & 63) == 0 && k_min != ~0u) atomicMin(&ctr->k_min, k_min);
 }
 
 // =======================================================================================
@@ -3012,7 +3016,7 @@ hipError_t launch_swarm_real(const InstanceDesc* d_desc, int precision, bool has
                              int ext, int block_size, int grid, int pending_trigger, size_t lds_bytes,
                              int ch_off, int cum_off, int64_t first, int64_t count, int flush,
                              const ParkedState* park_in, int64_t n_park_in, ParkedState* park_out,
-                             int64_t park_min, int park_lanes, int64_t tail0, uint32_t k_limit, int64_t park_cap, hipStream_t s,
+                             int64_t park_min, int park_lanes, int64_t tail0, uint32_t k_limit, uint32_t slice, int64_t park_cap, hipStream_t s,
                              TeamShape team) {
   const bool teams = team.lanes > 1 && !trace;
   void* fn = teams ? pick_team(precision, has_b, ext, true) : pick_kernel(precision, has_b, trace, true, ext);
@@ -3024,7 +3028,7 @@ hipError_t launch_swarm_real(const InstanceDesc* d_desc, int precision, bool has
   uint32_t scarce = 2u * (teams ? static_cast<uint32_t>(team.per_wave) : kClaimChunk) * static_cast<uint32_t>(grid * (block_size / 64));
   void* args[] = {const_cast<InstanceDesc**>(&d_desc), &pending_trigger, &ch_off, &cum_off, &first, &count, &flush,
                   const_cast<ParkedState**>(&park_in), &n_park_in, &park_out, &park_min, &park_lanes, &tail0,
-                  &team.lanes, &team.per_wave, &scarce, &k_limit, &cap};
+                  &team.lanes, &team.per_wave, &scarce, &k_limit, &slice, &cap};
   return hipLaunchKernel(fn, dim3(grid), dim3(block_size), args, lds_bytes, s);
 }
 

@@ -59,7 +59,7 @@ def test_team_lineages_equal_one_lane_lineages(gpu, precision):
     """Real secondaries: in slices of the lineage budget with eager and default parking, in whole
     generations (no parking), budgets around a slice's end, and a capacity that overflows."""
     cfg = synth.cfg3_mixture_real()
-    for n_e, n_c in ((3, 900), (700, 900), (40, 63), (40, 64), (40, 65), (4100, 130)):
+    for n_e, n_c in ((3, 900), (700, 900), (40, 63), (40, 64), (40, 65), (4100, 130), (30500, 260)):
         ref = None
         for shape in ({"park_lanes": -1, **ONE_LANE}, {"park_lanes": -1}, {}, ONE_LANE, {"park_lanes": 64}):
             s = gpu.Swarm.from_config(cfg, precision)
