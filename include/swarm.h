@@ -245,7 +245,7 @@ swarm_status swarm_create(const swarm_component* comps, int32_t n_comps,
 swarm_status swarm_run(swarm_t h, int64_t n_electrons, int64_t n_collisions, uint64_t seed);
 
 /* The run of swarm_run, started without waiting for it.  DUMMY mode enqueues all its device
- * work on the handle's stream (work items, the swarm kernel, the tally reductions) and
+ * work on the handle's stream (the swarm kernel, the tally reductions) and
  * returns; REAL mode runs its generations on a worker thread the handle owns, since each
  * generation's launch depends on the counters of the one before.  Errors found before the
  * work starts (arguments, allocation) are returned here; the run's own status (e.g.
@@ -262,7 +262,7 @@ swarm_status swarm_run_async(swarm_t h, int64_t n_electrons, int64_t n_collision
 swarm_status swarm_wait(swarm_t h);
 
 /* swarm_create with every device allocation of the handle (tables, records, secondary
- * queue, work items, tally buffers, trace buffers) taken from one region the caller owns:
+ * queue, tally buffers, trace buffers) taken from one region the caller owns:
  * `arena` is a device pointer to arena_bytes bytes (e.g. a torch tensor's data_ptr) that
  * must stay valid until swarm_destroy.  The library sub-allocates it (first fit, 256-byte
  * blocks) and never frees it.  A run that does not fit returns SWARM_ERR_OUT_OF_MEMORY;
@@ -313,7 +313,7 @@ swarm_status swarm_last_launches(swarm_t h, int64_t* launches, int64_t* parked);
  * loops that must not call hipMalloc, harnesses that forbid it): the DUMMY-mode run of
  * swarm_run with no allocation.  The caller passes `records`, device memory for n_electrons
  * swarm_record entries, which receive the records of ids 0..n-1 in id order (as swarm_run
- * keeps them).  The run's scratch (work items, their counter, tally partial sums and
+ * keeps them).  The run's scratch (tally tiles, partial sums and
  * output) is a library array of 1.4 MB in device memory, one per GPU, held until the
  * process ends; n_electrons is limited to 4194304 (2^22) and larger runs are refused with
  * SWARM_ERR_INVALID_ARG, as are REAL mode and tracing.  Every call on a GPU shares that
@@ -373,10 +373,9 @@ typedef struct swarm_batch* swarm_batch_t;
  * batch keeps the per-instance results on the device; swarm_batch_launch runs every job
  * in one persistent kernel (waves claim `chunk` electrons at a time, instance tables staged in
  * LDS), followed by the tally kernels, captured in a hipGraph when use_graph != 0.  The
- * first launch hands out the instances' items heaviest collision budget first, then in the
- * order given; swarm_batch_wait of the first launch orders them again by each instance's
- * measured work per electron (trials per real collision), longest first, for the launches
- * after it.  The order changes no result. */
+ * first launch shares its work-groups out by each instance's expected work;
+ * swarm_batch_wait of the first launch shares them out again by the measured work per electron
+ * (trials per real collision), for the launches after it.  Neither changes a result. */
 swarm_status swarm_batch_create(swarm_t* handles, const swarm_job* jobs, int32_t n,
                                 const swarm_launch_opts* opts, swarm_batch_t* out);
 swarm_status swarm_batch_launch(swarm_batch_t b);                  /* asynchronous */
@@ -391,7 +390,7 @@ swarm_status swarm_batch_run(swarm_t* handles, const swarm_job* jobs, int32_t n,
                              const swarm_launch_opts* opts);
 
 /* Autotuner: times the result-invariant launch options (block size, pending trigger, electrons
- * per work item, LDS table layout) on a shortened copy of the batch
+ * per claim, LDS table layout) on a shortened copy of the batch
  * (same instances, budgets cut to probe_collisions) and writes the fastest to *best. */
 swarm_status swarm_autotune(swarm_t* handles, const swarm_job* jobs, int32_t n,
                             int64_t probe_collisions, swarm_launch_opts* best);

@@ -626,12 +626,12 @@ __global__ void k_next_generation(RunCounters* ctr) {
 // Per-electron null-collision loop.
 // =======================================================================================
 
-// Instance constants in the working precision, loaded once per work item.
+// Instance constants in the working precision, loaded when a work-group takes an instance.
 template <typename R>
 struct Consts {
   R nup, cT, c_eps, c_speed, speed0, az, omega, bx, bz, vDy, apar;
   R omega_rev;   // omega / (2 pi): the gyration phase in revolutions
-  R inv_omega;   // 1 / omega (B > 0), divided once per work item instead of per collision
+  R inv_omega;   // 1 / omega (B > 0), divided once per instance instead of per collision
   R aze, apare;  // accelerations in energy units (FP32: times sqrt(m/2e); FP64: plain)
   R nup24;       // FP32: nu' 2^-24, FP64: nu' 2^-53 (x = R nu' straight from the integer)
   R Pf, twoPf;   // grid points per octave, and twice that, as floating point
@@ -712,8 +712,8 @@ __device__ __forceinline__ Consts<R> load_consts(const InstanceDesc& d) {
   c.wmask = (1u << (23 - d.p_log2)) - 1u;
   c.e_lo = __uint_as_float((static_cast<uint32_t>(127 + d.emin) << 23) - 1u);
   // The median-of-three of the index clamp can read one scalar operand only; a copy the
-  // compiler cannot rematerialise keeps the other bound in a vector register for the whole
-  // work item instead of a move in every trial.
+  // compiler cannot rematerialise keeps the other bound in a vector register for as
+  // long as the instance is run instead of a move in every trial.
   const float e_hi = __uint_as_float(static_cast<uint32_t>(127 + d.emax) << 23);
   asm("v_mov_b32 %0, %1" : "=v"(c.e_hi) : "s"(e_hi));
   asm("v_mov_b32 %0, %1" : "=v"(c.off1G_v) : "s"(c.off1G));
