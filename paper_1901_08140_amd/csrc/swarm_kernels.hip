@@ -1912,8 +1912,13 @@ __device__ __forceinline__ int next_instance(const InstanceDesc* __restrict__ de
 // Waves per SIMD the registers of the dummy kernel have to allow (asked for where the compiler
 // would end one or a few registers above the limit): FP32 5 (96 VGPRs), B with an adaptive trial
 // frequency 4 (128).
+// (FP64 with B needs 183 registers, two waves.  Held to 168, three waves with 56 B of spill: argon
+// at 0.7 T, 16 x 50,000 x 1000, 79 -> 71 ms, one argon point 200,000 x 1000 15.2 -> 13.4, one of
+// the mixture 300,000 x 800 14.7 -> 13.3, uneven mixtures 84 both.  The real-secondaries kernel,
+// held the same way, spilled 80 B and took 47.4 instead of 43.7 ms.)
 template <typename R, bool HB, bool TR, int EXT>
 constexpr int dummy_waves() {
+  if (sizeof(R) == 8 && HB && EXT == 0 && !TR) return 3;
   if (TR || sizeof(R) == 8 || EXT == 2) return 1;
   return HB && EXT == 1 ? 4 : 5;
 }
