@@ -182,6 +182,39 @@ struct InstanceDesc {
   double trials;
 };
 
+// How many electrons a wave takes at a time when `left` are left (as far as it knows) and its
+// idle lanes want `wanted`: `chunk` while more than `scarce` are left, then `share` of what is
+// left, and never fewer than it wants.  Every claim is an atomic on the launch's one counter
+// that the wave waits for.  The generations of a real-secondaries run take shares: with only what
+// their lanes wanted (share 0) from two chunks per wave on, a generation of two or three
+// rounds made a claim for nearly every electron (FP32, wanted only | shares, ms: 1e6 primaries x 300
+// in argon at 30 Td 10.4 | 9.5, in Ar:CO2 at 100 Td 19.2 | 16.6; 1e6 x 100 in argon at 100 Td 9.0 |
+// 7.5; 1e5 x 2000 of the magnetised mixture 64.5 | 61.4).  Dummy launches take what they want: they
+// end on finer steps that way (argon sweep 32 x 1e5 x 2e4 FP32 727 ms, with shares 733; FP64 of one
+// magnetised mixture, 4e5 x 500, 11.4 | 13.1), and electrons that end often are held up by
+// their count in RunCounters::n_done sooner than by claims.
+struct ClaimRule {
+  uint32_t chunk = 1, scarce = 0;
+  float share = 0.0f;
+  __host__ __device__ uint32_t size(uint32_t left, uint32_t wanted) const {
+    if (left > scarce) return chunk;
+    const uint32_t n = static_cast<uint32_t>(static_cast<float>(left) * share);
+    return n > wanted ? n : wanted;
+  }
+};
+// From `chunks` more claims of every wave on: no more than its idle lanes want, or with
+// `shares` a part of an even share of what is left (a `chunks`-th of it, so that the sizes go
+// on from the chunk).
+inline ClaimRule claim_rule(uint32_t chunk, int64_t waves, int chunks, bool shares) {
+  ClaimRule r;
+  const uint64_t all = static_cast<uint64_t>(chunks) * static_cast<uint64_t>(waves);
+  const uint64_t scarce = all * chunk;
+  r.chunk = chunk;
+  r.scarce = scarce < 0xffffffffull ? static_cast<uint32_t>(scarce) : 0xffffffffu;
+  r.share = shares ? 1.0f / static_cast<float>(all) : 0.0f;
+  return r;
+}
+
 // How a launch hands out the electrons of its instances.  Every instance has a counter of
 // those taken (64 bytes apart); a wave takes some at a time and passes them to its lanes.
 // A work-group starts with instance first[blockIdx.x] (NULL: instance 0), stays with it until
@@ -193,8 +226,8 @@ struct ClaimPlan {
   const int32_t* first;
   const float* weight;
   int32_t n_inst;
-  int32_t chunk;                          // electrons a wave takes at a time while many are left
-  uint32_t scarce = 0;                    // from this many on: no more than its idle lanes need
+  int32_t chunk;                          // the rule's chunk (launches of teams set their own)
+  ClaimRule rule = {};
 };
 
 struct TallyTile {

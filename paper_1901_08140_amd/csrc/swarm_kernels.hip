@@ -1831,10 +1831,10 @@ __device__ __forceinline__ int64_t wave_uniform(int64_t x) {
 }
 
 // The electrons a wave has taken and not yet given to a lane, [next, end), and whether none
-// are left to take.  While many are left a wave takes `chunk` at a time, so that lanes rarely
-// wait on the device-wide counter; towards the end (left <= scarce) it takes only what its idle
-// lanes need, so that no wave holds electrons that another could run.  (32 bits: the records of
-// 2^32 electrons would not fit the device.)
+// are left to take.  While many are left a wave takes a chunk at a time, so that lanes rarely
+// wait on the device-wide counter; towards the end it takes less, so that no wave holds electrons
+// that another could run (ClaimRule).  (32 bits: the records of 2^32 electrons would not fit
+// the device.)
 struct WaveClaim {
   uint32_t next = 0, end = 0;
   bool none = false;
@@ -1843,13 +1843,12 @@ struct WaveClaim {
 // Electrons for the wave's idle lanes (with teams for the first lane of each, `firsts`): true,
 // with the electron's index in *e, for a lane that got one.
 __device__ __forceinline__ bool claim_electron(WaveClaim& w, bool is_idle, uint64_t idle, uint64_t firsts, int sub,
-                                               unsigned long long* taken, uint32_t count, uint32_t chunk, uint32_t scarce,
-                                               uint32_t* e) {
+                                               unsigned long long* taken, uint32_t count, const ClaimRule& rule, uint32_t* e) {
   const uint64_t asking = idle & firsts;
   const uint32_t wanted = static_cast<uint32_t>(__popcll(asking));
   if (w.next >= w.end && !w.none) {
     const int leader = __ffsll(static_cast<long long>(idle)) - 1;
-    const uint32_t n = count - w.end > scarce ? chunk : wanted;
+    const uint32_t n = rule.size(count - w.end, wanted);
     unsigned long long base = 0;
     if (static_cast<int>(__lane_id()) == leader) base = atomicAdd(taken, static_cast<unsigned long long>(n));
     const uint32_t got = __builtin_amdgcn_readfirstlane(
@@ -1968,7 +1967,7 @@ __global__ void __launch_bounds__(512, (dummy_waves<R, HB, TR, EXT>())) k_swarm_
       const uint64_t idle = __ballot(L.state == ST_IDLE);
       if (idle != 0) {
         uint32_t ei;
-        const bool got = claim_electron(claims, L.state == ST_IDLE, idle, ~0ull, 0, taken, count, plan.chunk, plan.scarce, &ei);
+        const bool got = claim_electron(claims, L.state == ST_IDLE, idle, ~0ull, 0, taken, count, plan.rule, &ei);
         if (got) {
           const uint32_t started = d.saved != nullptr ? d.saved[ei].started : 0u;
           if (started != 2u) {          // 2: finished in an earlier launch
@@ -2153,7 +2152,7 @@ __global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restri
       const uint64_t idle = __ballot(L.state == ST_IDLE);
       if (idle != 0) {
         uint32_t ei;
-        const bool got = claim_electron(claims, L.state == ST_IDLE, idle, firsts, team.sub, taken, count, plan.chunk, plan.scarce, &ei);
+        const bool got = claim_electron(claims, L.state == ST_IDLE, idle, firsts, team.sub, taken, count, plan.rule, &ei);
         if (got) {
           const uint32_t started = d.saved != nullptr ? d.saved[ei].started : 0u;
           if (started != 2u) {          // 2: finished in an earlier launch
@@ -2418,7 +2417,7 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
         const uint64_t idle = __ballot(L.state == ST_IDLE);
         if (idle != 0) {
           uint32_t ei;
-          const bool got = claim_electron(claims, L.state == ST_IDLE, idle, ~0ull, 0, taken, count, plan.chunk, plan.scarce, &ei);
+          const bool got = claim_electron(claims, L.state == ST_IDLE, idle, ~0ull, 0, taken, count, plan.rule, &ei);
           if (got) {
             const uint32_t started = d.saved != nullptr ? d.saved[ei].started : 0u;
             if (started != 2u) {
@@ -2489,7 +2488,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
                                                     int flush, const ParkedState* __restrict__ park_in,
                                                     int64_t n_park_in, ParkedState* __restrict__ park_out,
                                                     int64_t park_min, int park_lanes, int64_t tail0,
-                                                    int g, int per_wave, uint32_t scarce, uint32_t k_limit,
+                                                    int g, int per_wave, ClaimRule rule, uint32_t k_limit,
                                                     uint32_t slice, uint32_t park_cap) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -2519,7 +2518,6 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
   // lane's electron
   const uint64_t firsts = TEAM ? __ballot(team.sub == 0) : ~0ull;
   const uint64_t lane_lt = ((1ull << team.base) - 1ull) & firsts;
-  const uint32_t claim = TEAM ? static_cast<uint32_t>(per_wave) : kClaimChunk;
   // wave-uniform: the wave's electrons, whether the run is stopping after an overflow, and the
   // pass count
   const int64_t total = n_park_in + count;   // parked electrons first, then the generation's
@@ -2533,7 +2531,7 @@ __global__ void __launch_bounds__(512) k_swarm_real(const InstanceDesc* __restri
       uint32_t e;
       const bool got = claim_electron(claims, L.state == ST_IDLE, idle, firsts, team.sub,
                                       reinterpret_cast<unsigned long long*>(&ctr->gen_next), static_cast<uint32_t>(total),
-                                      claim, scarce, &e);
+                                      rule, &e);
       if (L.state == ST_IDLE && !got && claims.none) L.state = ST_DONE;
       if (got) {
         if (e < n_park_in) {
@@ -2999,8 +2997,8 @@ hipError_t launch_swarm_dummy(const InstanceDesc* d_desc, ClaimPlan plan, int pr
                               size_t lds_bytes, int ch_off, int pool_off, int cum_off, hipStream_t s, TeamShape team) {
   const bool teams = team.lanes > 1 && !trace && service_waves == 0;
   if (teams) plan.chunk = team.per_wave;
-  // electrons for two more claims of every wave
-  plan.scarce = 2u * static_cast<uint32_t>(plan.chunk) * static_cast<uint32_t>(grid * ((teams ? team.block : block_size) / 64));
+  plan.rule = claim_rule(static_cast<uint32_t>(plan.chunk), static_cast<int64_t>(grid) * ((teams ? team.block : block_size) / 64),
+                         2, false);
   if (service_waves > 0 && !trace) {
     if (service_waves >= block_size / 64) return hipErrorInvalidValue;
     void* fn = pick_pooled(precision, has_b, ext);
@@ -3030,10 +3028,11 @@ hipError_t launch_swarm_real(const InstanceDesc* d_desc, int precision, bool has
     pending_trigger = team.trigger;
   }
   uint32_t cap = static_cast<uint32_t>(std::min<int64_t>(park_cap, 0xffffffffLL));
-  uint32_t scarce = 2u * (teams ? static_cast<uint32_t>(team.per_wave) : kClaimChunk) * static_cast<uint32_t>(grid * (block_size / 64));
+  ClaimRule rule = claim_rule(teams ? static_cast<uint32_t>(team.per_wave) : kClaimChunk,
+                              static_cast<int64_t>(grid) * (block_size / 64), 4, true);
   void* args[] = {const_cast<InstanceDesc**>(&d_desc), &pending_trigger, &ch_off, &cum_off, &first, &count, &flush,
                   const_cast<ParkedState**>(&park_in), &n_park_in, &park_out, &park_min, &park_lanes, &tail0,
-                  &team.lanes, &team.per_wave, &scarce, &k_limit, &slice, &cap};
+                  &team.lanes, &team.per_wave, &rule, &k_limit, &slice, &cap};
   return hipLaunchKernel(fn, dim3(grid), dim3(block_size), args, lds_bytes, s);
 }
 
