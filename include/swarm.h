@@ -309,6 +309,12 @@ swarm_status swarm_last_timing(swarm_t h, double* kernel_ms, double* total_ms);
  * may be NULL.  SWARM_ERR_STATE before the first completed run. */
 swarm_status swarm_last_launches(swarm_t h, int64_t* launches, int64_t* parked);
 
+/* Lanes that ran each electron of the last run together (the most of its launches in REAL
+ * mode): 1, or 2 to 16 where a launch held too few electrons to fill the device with one lane
+ * each and the caller left its shape to the library.  No result depends on it.
+ * SWARM_ERR_STATE before the first completed run. */
+swarm_status swarm_last_team(swarm_t h, int32_t* lanes);
+
 /* For callers that cannot allocate device memory (code under HIP graph capture, serving
  * loops that must not call hipMalloc, harnesses that forbid it): the DUMMY-mode run of
  * swarm_run with no allocation.  The caller passes `records`, device memory for n_electrons

@@ -135,6 +135,7 @@ _SIGS = {
     "swarm_tables": (_i32, [_vp, _P(_i32), _P(_i32), _P(_d), _P(_d), _P(_d)]),
     "swarm_last_timing": (_i32, [_vp, _P(_d), _P(_d)]),
     "swarm_last_launches": (_i32, [_vp, _P(_i64), _P(_i64)]),
+    "swarm_last_team": (_i32, [_vp, _P(_i32)]),
     "swarm_destroy": (None, [_vp]),
     "swarm_strerror": (ctypes.c_char_p, [_i32]),
     "swarm_last_error": (ctypes.c_char_p, []),
@@ -344,6 +345,13 @@ def swarm_last_launches(h):
     return n.value, p.value
 
 
+def swarm_last_team(h):
+    """Lanes per electron of the last run (the most of its launches)."""
+    n = _i32(0)
+    _check(_lib.swarm_last_team(h, ctypes.byref(n)))
+    return n.value
+
+
 def swarm_destroy(h):
     if h:
         _lib.swarm_destroy(h)
@@ -534,6 +542,9 @@ class Swarm:
 
     def launches(self):
         return swarm_last_launches(self.h)
+
+    def team(self):
+        return swarm_last_team(self.h)
 
     def set_trace(self, ids, max_events):
         self._trace = swarm_set_trace(self.h, ids, max_events)

@@ -846,6 +846,7 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     if ((e = launch_swarm_dummy(h->d_desc, plan, d.precision, h->has_b, trace, ext, svc, o.block_size, grid, o.pending_trigger,
                                 lds, ch_off, ll.pool_off, ll.cum_off, s, team)) != hipSuccess)
       return hip_fail(e, "swarm kernel launch");
+    h->team_lanes = team.lanes;
     h->n_launches = 1;
     h->n_parked = 0;
   }
@@ -901,6 +902,7 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     int64_t first = -1, count = n_electrons, queued = 0, n_parked = 0;
     h->n_launches = 0;
     h->n_parked = 0;
+    h->team_lanes = 1;
     for (;;) {
       if ((e = launch_next_generation(d.ctr, s)) != hipSuccess) return hip_fail(e, "generation counters");
       const int64_t electrons = n_parked + count;
@@ -922,6 +924,7 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
                                  park_min, park_lanes, queued, static_cast<uint32_t>(limit), sliced ? static_cast<uint32_t>(slice) : 0u, park_cap, s, team)) != hipSuccess)
         return hip_fail(e, "swarm kernel launch");
       h->n_launches += 1;
+      h->team_lanes = std::max(h->team_lanes, team.lanes);
       if ((e = hipMemcpyAsync(&hc, d.ctr, sizeof(hc), hipMemcpyDeviceToHost, s)) != hipSuccess) return hip_fail(e, "counters");
       if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "swarm kernel");
       const int64_t tail = std::min<int64_t>(static_cast<int64_t>(hc.child_tail), child_cap);
@@ -1107,6 +1110,14 @@ swarm_status swarm_last_launches(swarm_t h, int64_t* launches, int64_t* parked) 
   if (!h->have_run) return fail(SWARM_ERR_STATE, "no completed run");
   if (launches) *launches = h->n_launches;
   if (parked) *parked = h->n_parked;
+  return SWARM_OK;
+}
+
+swarm_status swarm_last_team(swarm_t h, int32_t* lanes) {
+  if (!h || !lanes) return fail(SWARM_ERR_INVALID_ARG, "NULL argument");
+  if (h->in_flight) return busy();
+  if (!h->have_run) return fail(SWARM_ERR_STATE, "no completed run");
+  *lanes = h->team_lanes;
   return SWARM_OK;
 }
 

@@ -138,6 +138,7 @@ struct swarm {
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
   double kernel_ms = 0.0, total_ms = 0.0;
   int64_t n_launches = 0, n_parked = 0;     // the last run's simulation launches, parked electrons
+  int team_lanes = 1;                       // the last run's lanes per electron (the most of its launches)
   swarm_launch_opts opts{};
   bool free_shape = true;                   // no launch shape was asked for
   // a run started by swarm_run_async: 1 enqueued on the stream (dummy mode), 2 running on

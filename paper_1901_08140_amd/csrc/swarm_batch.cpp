@@ -234,6 +234,7 @@ swarm_status swarm_batch_wait(swarm_batch_t b, double* device_ms) {
     h->total_ms = ms;
     h->n_launches = 1;
     h->n_parked = 0;
+    h->team_lanes = b->team.lanes;
   }
   b->done = true;
   if (!b->reordered) {
