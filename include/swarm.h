@@ -364,8 +364,9 @@ typedef struct {
                               wave with at most this many running lanes parks them (each at its
                               next real collision) for the next launch, if the launch has
                               created secondaries for an eighth of the device; 0: 32, at most
-                              64.  -1: never, and launches of few electrons, which otherwise
-                              run in slices of the budget and are parked in between, run whole
+                              64.  -1: never, and launches of few electrons of a gas that
+                              ionises, which otherwise run in slices of the budget (longer ones
+                              where it ionises little) and are parked in between, run whole
                               generations */
 } swarm_launch_opts;
 

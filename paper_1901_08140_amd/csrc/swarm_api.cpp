@@ -858,12 +858,7 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     // one before, so there are at most n_collisions + 1.  After an overflow the next launch
     // records the queued secondaries unstarted (flag 8) and creates none.
     //
-    // A generation by itself lasts as long as its longest electron, so while few electrons are
-    // left a run would spend its time on a few long chains, generation after generation.  A
-    // launch of few electrons therefore runs them only up to a common lineage count, parks them
-    // there, and the next launch resumes them together with the secondaries, which have caught up
-    // by its end.  That holds from the start up to kSliceGrowing electrons, and again once the
-    // generations have shrunk to kSliceLast, from the smallest lineage count left.  (Ar:CO2
+    // Small runs, and the ends of all, go in slices of the lineage budget (SlicePlan).  Ar:CO2
     // mixture, ms with whole generations and with slices of 64, 128, 256 collisions from the start,
     // at 1 T: 500 primaries x 1500, FP32 18.0, 8.4, 10.0, 12.0, FP64 31.5, 13.7, 16.4, 20.6; 5000 x
     // 1500, FP32 23.0, 16.2, 14.9, 17.4, FP64 38.9, 23.7, 25.0, 27.6.  With up to 100,000 electrons
@@ -871,7 +866,11 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     // 64.8, 50,000 x 1000 at B = 0 16.2 and 14.8.  With up to 30,000, 50,000 and 100,000 at the start
     // and 100,000 at the end: the same runs 65.4, 65.4, 64.8 and 14.4, 15.0, 14.8, FP64 20,000 x
     // 1000 17.8, 17.2, 20.1 and 60,000 x 600 8.7, 8.6, 11.8; with 200,000 at the end 66.0, 15.3, 20.1
-    // and 11.8, with 50,000 67.5, 14.4, 18.9 and 9.0.)
+    // and 11.8, with 50,000 67.5, 14.4, 18.9 and 9.0.
+    // Where little is ionised, FP32 with whole generations, slices of 64 or 128 throughout and
+    // growing ones: the mixture at 5 Td, 20,000 x 3000, 11.5, 21.2, 13.4, argon at 10 Td, 5000 x
+    // 5000, 10.1, 18.0, 12.3, at 50 Td, 1000 x 10,000 (11,600 electrons in the end), 102, 38.7, 38.4,
+    // the Maxwell gas, 30,000 x 3000, 2.8, 12.1 and never sliced.
     //
     // Beyond that, a launch that has created secondaries for at least an eighth of the device's
     // lanes lets its last few running electrons park (1e6 primaries: FP32 399 -> 372 ms, FP64
@@ -881,13 +880,13 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     // No more than four waves per SIMD: the collisions of a magnetised mixture wait on L2, and the
     // channel rows of more waves crowd it (100,000 primaries 73.3 ms with five, 70.4 with four, 72.0
     // with three; 1e6 primaries x 1000 76.6 and 72.4 with five and four).
-    constexpr int64_t kSliceGrowing = 30'000, kSliceLast = 100'000;
     const int groups_per_cu = std::max(1, std::min(per_cu, 16 * 64 / o.block_size));
     const int64_t lanes = static_cast<int64_t>(dev.n_cu) * groups_per_cu * o.block_size;
     const int park_lanes = std::max(0, o.park_lanes);   // -1: never
     // (where memory cannot hold the parked electrons of slices, those of a launch's end)
     const int64_t end_cap = parked_capacity(lanes, park_lanes);
-    int64_t park_cap = park_lanes == 0 ? end_cap : std::max(end_cap, std::min(capacity, kSliceLast));
+    const int64_t slice_lanes = static_cast<int64_t>(dev.n_cu) * 4 * 4 * 64;
+    int64_t park_cap = park_lanes == 0 ? end_cap : std::max(end_cap, std::min(capacity, slice_lanes / 8 * 3));
     e = h->parked.ensure(2 * static_cast<size_t>(park_cap) * sizeof(ParkedState));
     if (e == hipErrorOutOfMemory && park_cap > end_cap) {
       (void)hipGetLastError();
@@ -897,8 +896,8 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     if (e != hipSuccess) return hip_fail(e, "allocating parked electrons");
     ParkedState* park_in = static_cast<ParkedState*>(h->parked.p);
     ParkedState* park_out = park_in + park_cap;
-    int64_t reached = 0;            // lineage count that the electrons of the next launch have reached
-    bool growing = true;            // no launch has run whole generations yet
+    const bool ionises = std::find(h->kinds.begin(), h->kinds.end(), SWARM_IONIZATION) != h->kinds.end();
+    SlicePlan slices = {n_collisions, slice_lanes, park_cap, ionises && park_lanes > 0};
     int64_t first = -1, count = n_electrons, queued = 0, n_parked = 0;
     h->n_launches = 0;
     h->n_parked = 0;
@@ -913,15 +912,13 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
       const int grid = team.lanes > 1
           ? team_grid(team, (electrons + team.per_group() - 1) / team.per_group())
           : static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want, static_cast<int64_t>(dev.n_cu) * groups_per_cu)));
-      const bool sliced = park_lanes > 0 && electrons <= std::min(park_cap, growing ? kSliceGrowing : kSliceLast);
-      growing = growing && sliced;
-      const int64_t slice = electrons <= 4000 ? 64 : 128;
-      const int64_t limit = sliced ? std::min(reached + slice, n_collisions) : n_collisions;
+      const int64_t limit = slices.limit(electrons);
+      const uint32_t slice = slices.sliced ? static_cast<uint32_t>(std::min(slices.length, n_collisions)) : 0u;
       const int64_t park_min = hc.dropped != 0 || park_lanes == 0 ? 0 : std::max<int64_t>(1, lanes / 8);
       if ((e = launch_swarm_real(h->d_desc, d.precision, h->has_b, trace, ext, o.block_size, grid,
                                  o.pending_trigger ? o.pending_trigger : kRealTrigger, lds,
                                  ch_off, ll.cum_off, first, count, hc.dropped != 0 ? 1 : 0, park_in, n_parked, park_out,
-                                 park_min, park_lanes, queued, static_cast<uint32_t>(limit), sliced ? static_cast<uint32_t>(slice) : 0u, park_cap, s, team)) != hipSuccess)
+                                 park_min, park_lanes, queued, static_cast<uint32_t>(limit), slice, park_cap, s, team)) != hipSuccess)
         return hip_fail(e, "swarm kernel launch");
       h->n_launches += 1;
       h->team_lanes = std::max(h->team_lanes, team.lanes);
@@ -933,7 +930,7 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
       count = tail - queued;
       queued = tail;
       n_parked = std::min<int64_t>(static_cast<int64_t>(hc.parked), park_cap);
-      reached = sliced ? limit : static_cast<int64_t>(hc.k_min);
+      slices.launched(electrons, count, limit, static_cast<int64_t>(hc.k_min));
       h->n_parked += n_parked;
       std::swap(park_in, park_out);
     }

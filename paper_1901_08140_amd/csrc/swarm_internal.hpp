@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "../../include/swarm.h"
 
 namespace swarm_impl {
@@ -214,6 +216,47 @@ inline ClaimRule claim_rule(uint32_t chunk, int64_t waves, int chunks, bool shar
   r.share = shares ? 1.0f / static_cast<float>(all) : 0.0f;
   return r;
 }
+
+// Slices of the lineage budget in a real-secondaries run.  A generation by itself lasts as long
+// as its longest electron, so while few electrons are left a run would spend its time on a few
+// long chains, generation after generation.  A launch of few electrons therefore runs them only
+// up to a common lineage count, parks them there, and the next launch resumes them together with
+// the secondaries, which have caught up by its end.  That holds from the start while the run is
+// small (for the device's `lanes`, four waves per SIMD), and again once the generations have
+// shrunk, from the smallest lineage count left.
+// A slice costs a launch and a wait for its slowest electron (20,000 electrons that ionise
+// nothing, FP32: 0.4 ms for 128 collisions that take 0.5), and it gains nothing where no
+// generation follows.  A gas without ionisation is never sliced.  A slice is doubled while fewer
+// than a hundredth of its electrons (of the few that do not fill a wave per SIMD, for which
+// slices cost less, a four-hundredth) ionise in it, both in the last one and by the rate
+// counted so far, and it is short again when a twenty-fifth do in one.
+struct SlicePlan {
+  int64_t budget, lanes, room;      // collisions of a lineage; parked electrons that fit
+  bool ionises;                     // the gas has an ionisation channel (and parking is allowed)
+  int64_t reached = 0;              // lineage count that the electrons of the next launch have reached
+  int64_t length = 0;               // of a slice, 0: the shortest
+  bool growing = true;              // no launch has run whole generations yet
+  bool sliced = false;              // the launch under way
+  double born = 0.0, work = 0.0;    // secondaries and electron-collisions counted at `length` or below
+  // The lineage count at which a launch of `electrons` parks them.
+  int64_t limit(int64_t electrons) {
+    sliced = ionises && electrons <= room && electrons <= (growing ? lanes / 8 : lanes / 8 * 3);
+    growing = growing && sliced;
+    if (!sliced || length == 0) length = 0, born = work = 0.0;
+    length = std::max<int64_t>(length, electrons <= lanes / 64 ? 64 : 128);
+    return sliced && budget - reached > length ? reached + length : budget;
+  }
+  // What that launch did: secondaries made, smallest lineage count left.
+  void launched(int64_t electrons, int64_t made, int64_t at, int64_t smallest) {
+    reached = sliced ? at : smallest;
+    if (!sliced) return;
+    born += static_cast<double>(made);
+    work += static_cast<double>(electrons) * static_cast<double>(length);
+    const int64_t few = electrons <= lanes / 64 ? 400 : 100;
+    if (made * 25 > electrons) length = 0;
+    else if (made * few < electrons && (born + 1.0) * static_cast<double>(few * length) < work && length < budget) length *= 2;
+  }
+};
 
 // How a launch hands out the electrons of its instances.  Every instance has a counter of
 // those taken (64 bytes apart); a wave takes some at a time and passes them to its lanes.

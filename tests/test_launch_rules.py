@@ -41,6 +41,22 @@ static void simulate(const char* name, uint64_t electrons, int64_t waves, uint32
   printf("%s %llu %llu\n", name, (unsigned long long)claims, (unsigned long long)late);
 }
 
+// Launches of a run whose electrons each make `rate` secondaries per collision, the longest slice,
+// and whether every limit lies in the budget and beyond the one before.
+static void slices(const char* name, SlicePlan p, int64_t electrons, double rate) {
+  int64_t n = 0, at = 0, longest = 0, good = 1;
+  while (at < p.budget) {
+    const int64_t to = p.limit(electrons);
+    if (to <= at || to > p.budget) good = 0;
+    if (to - at > longest) longest = to - at;
+    p.launched(electrons, static_cast<int64_t>(static_cast<double>(electrons) * rate * static_cast<double>(to - at)), to, to);
+    at = to;
+    ++n;
+    if (!good) break;
+  }
+  printf("%s %lld %lld %lld\n", name, (long long)n, (long long)longest, (long long)good);
+}
+
 int main() {
   simulate("real", 1000000, 4096, 2, claim_rule(64, 4096, 4, true));
   simulate("dummy", 1000000, 4096, 2, claim_rule(64, 4096, 2, false));
@@ -48,6 +64,11 @@ int main() {
     const ClaimRule r = claim_rule(chunk, 8192, 2, false);
     printf("scarce%u %u\n", chunk, r.scarce);
   }
+  slices("none", {20000, 262144, 100000, true}, 20000, 0.0);
+  slices("many", {20000, 262144, 100000, true}, 500, 0.01);
+  slices("gas", {20000, 262144, 100000, false}, 500, 0.01);
+  slices("longest", {0xffffffffll, 262144, 100000, true}, 25, 0.0);
+  slices("short", {40, 262144, 100000, true}, 25, 0.0);
   const ClaimRule r = claim_rule(64, 1, 4, true);
   printf("sizes %u %u %u %u\n", r.size(1u << 31, 3), r.size(257, 3), r.size(100, 3), r.size(0, 3));
   return 0;
@@ -88,3 +109,13 @@ def test_the_end_of_a_launch_is_known_for_any_chunk(host_output):
 
 def test_claim_sizes(host_output):
     assert host_output["sizes"] == [64, 64, 25, 3]
+
+
+def test_slices_of_the_budget(host_output):
+    """Doubled from 128 without secondaries, the shortest where many are made, the whole budget
+    for a gas that makes none or a budget that one slice holds."""
+    assert host_output["none"] == [8, 8192, 1]          # 128 + 256 + ... + 8192 + the rest
+    assert host_output["many"] == [313, 64, 1]          # 20000 / 64
+    assert host_output["gas"] == [1, 20000, 1]
+    assert host_output["short"] == [1, 40, 1]
+    assert host_output["longest"][0] <= 26 * 33 and host_output["longest"][2] == 1
