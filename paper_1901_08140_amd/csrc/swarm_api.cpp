@@ -354,7 +354,7 @@ double electron_work(double n_collisions, double trials, int team_lanes) {
 // work-groups as that needs (all of its electrons at once where w is near T or above).  The
 // longest electrons come first; instances that find no work-group left start when one is free.
 // A work-group keeps its instance, with no wait between electrons, until the instance's
-// electrons are all taken, and then helps where most work is left (next_instance).  Against
+// electrons are all taken, and then helps another (next_instance).  Against
 // a share in proportion to the work alone (ms): 16 adaptive argon swarms of 50,000 electrons,
 // 2.4 a lane, 55.4 | 51.6, as it makes whole rounds; 40 uneven swarms of up to 10,000 electrons
 // 33.2 | 29.5, as the longest electrons all start first; 20 argon fields x 60,000 93 | 94.
@@ -370,9 +370,9 @@ LaunchPlan plan_launch(const std::vector<int64_t>& n_e, const std::vector<double
     most[i] = (n_e[i] + per_group - 1) / per_group;
     groups += most[i];
     total += static_cast<double>(most[i]) * work[i];
-    p.weight.push_back(std::max(1e-30f, static_cast<float>(work[i])));
   }
   p.grid = static_cast<int>(std::max<int64_t>(1, std::min(groups, slots)));
+  p.n_inst = static_cast<int32_t>(n);
   const double T = 0.9 * total / p.grid;     // (a margin: the work is an estimate)
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
   int64_t left = p.grid;
@@ -386,23 +386,28 @@ LaunchPlan plan_launch(const std::vector<int64_t>& n_e, const std::vector<double
     given[i] += more;
     left -= more;
   }
-  for (int i : order) p.first.insert(p.first.end(), given[i], i);
+  for (int i : order) p.lists.insert(p.lists.end(), given[i], static_cast<uint32_t>(i));
+  for (double w : work) {
+    const float f = std::max(1e-30f, static_cast<float>(w));
+    uint32_t bits;
+    std::memcpy(&bits, &f, sizeof(bits));
+    p.lists.push_back(bits);
+  }
+  for (int64_t ne : n_e) p.lists.push_back(static_cast<uint32_t>(ne));
   return p;
 }
 
 hipError_t LaunchPlan::upload(void* base, hipStream_t s) const {
-  char* b = static_cast<char*>(base) + counter_words() * 8;
-  hipError_t e = hipMemcpyAsync(b, first.data(), first.size() * 4, hipMemcpyHostToDevice, s);
-  if (e != hipSuccess) return e;
-  return hipMemcpyAsync(b + first.size() * 4, weight.data(), weight.size() * 4, hipMemcpyHostToDevice, s);
+  return hipMemcpyAsync(static_cast<char*>(base) + counter_words() * 8, lists.data(), lists.size() * 4, hipMemcpyHostToDevice, s);
 }
 hipError_t LaunchPlan::clear(void* base, hipStream_t s) const {
   return launch_fill_u64(static_cast<uint64_t*>(base), 0ull, static_cast<int64_t>(counter_words()), s);
 }
 ClaimPlan LaunchPlan::view(void* base, int32_t chunk) const {
-  char* b = static_cast<char*>(base) + counter_words() * 8;
-  return {static_cast<unsigned long long*>(base), reinterpret_cast<const int32_t*>(b),
-          reinterpret_cast<const float*>(b + first.size() * 4), n_inst(), chunk};
+  const uint32_t* first = reinterpret_cast<const uint32_t*>(static_cast<char*>(base) + counter_words() * 8);
+  const uint32_t* weight = first + grid;
+  return {static_cast<unsigned long long*>(base), reinterpret_cast<const int32_t*>(first),
+          reinterpret_cast<const float*>(weight), weight + n_inst, n_inst, chunk};
 }
 int32_t wave_chunk(const swarm_launch_opts& o) { return std::max(1, o.chunk / (o.block_size / 64)); }
 
@@ -842,7 +847,7 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     const int64_t groups = (n_electrons + per_group - 1) / per_group;
     const int grid = team.lanes > 1 ? team_grid(team, groups)
                                     : static_cast<int>(std::min<int64_t>(groups, static_cast<int64_t>(dev.n_cu) * per_cu));
-    const ClaimPlan plan = {reinterpret_cast<unsigned long long*>(&d.ctr->gen_next), nullptr, nullptr, 1, wave_chunk(o)};
+    const ClaimPlan plan = {reinterpret_cast<unsigned long long*>(&d.ctr->gen_next), nullptr, nullptr, nullptr, 1, wave_chunk(o)};
     if ((e = launch_swarm_dummy(h->d_desc, plan, d.precision, h->has_b, trace, ext, svc, o.block_size, grid, o.pending_trigger,
                                 lds, ch_off, ll.pool_off, ll.cum_off, s, team)) != hipSuccess)
       return hip_fail(e, "swarm kernel launch");

@@ -82,14 +82,13 @@ struct LdsLayout {
 LdsLayout lds_layout(int precision, int G, int nc, int service_waves, int table_layout);
 // The work-groups of a launch over several instances: how many (at most `slots` resident ones,
 // per_group electrons at once in each) and which instance each starts with, given the expected
-// work per electron.  Held in device memory behind the counters of the electrons taken.
+// work per electron.  Held in device memory behind the counters of the instances.
 struct LaunchPlan {
   int grid = 1;
-  std::vector<int32_t> first;       // grid entries
-  std::vector<float> weight;        // per instance
-  int32_t n_inst() const { return static_cast<int32_t>(weight.size()); }
-  size_t counter_words() const { return weight.size() * kClaimStride; }
-  size_t bytes() const { return counter_words() * 8 + first.size() * 4 + weight.size() * 4; }
+  int32_t n_inst = 0;
+  std::vector<uint32_t> lists;      // first (grid), weight and count (n_inst each)
+  size_t counter_words() const { return static_cast<size_t>(n_inst) * kClaimStride; }
+  size_t bytes() const { return counter_words() * 8 + lists.size() * 4; }
   // Copies the lists behind the counters of `base` (bytes() long); the plan has to outlive the copy.
   hipError_t upload(void* base, hipStream_t s) const;
   hipError_t clear(void* base, hipStream_t s) const;        // no electron taken

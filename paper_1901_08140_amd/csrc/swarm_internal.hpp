@@ -258,16 +258,18 @@ struct SlicePlan {
   }
 };
 
-// How a launch hands out the electrons of its instances.  Every instance has a counter of
-// those taken (64 bytes apart); a wave takes some at a time and passes them to its lanes.
-// A work-group starts with instance first[blockIdx.x] (NULL: instance 0), stays with it until
-// all of its electrons are taken and run, and goes on with the instance that has the most work
-// left, weight (expected work per electron) times electrons not taken.
+// How a launch hands out the electrons of its instances.  Every instance has a line of 64 bytes
+// with the number of those taken and, behind it, of the work-groups that came to it; a wave takes
+// some electrons at a time and passes them to its lanes.  A work-group starts with instance
+// first[blockIdx.x] (NULL: instance 0), stays with it until all of its electrons are taken and
+// run, and goes on with an instance that has much work left for the work-groups on it: weight
+// (expected work per electron) times electrons not taken (next_instance).
 constexpr int kClaimStride = 8;           // counters are this many 64-bit words apart
 struct ClaimPlan {
   unsigned long long* taken;
   const int32_t* first;
   const float* weight;
+  const uint32_t* count;                  // electrons per instance
   int32_t n_inst;
   int32_t chunk;                          // the rule's chunk (launches of teams set their own)
   ClaimRule rule = {};

@@ -1887,25 +1887,73 @@ __device__ __forceinline__ void stage_instance(const InstanceDesc& d, unsigned c
   stage_cum<R>(d, smem, cum_off);
 }
 
-// The instance a work-group goes on with: the one with the most work not taken, or -1.
-__device__ __forceinline__ int next_instance(const InstanceDesc* __restrict__ descs, const ClaimPlan& plan,
-                                             unsigned long long* s_best) {
-  if (plan.n_inst == 1) return -1;
+// The instance a work-group goes on with, or -1: the one with the most work not taken per
+// work-group on it (the new one counted) among kHelpAmong instances, the work-group's own part
+// of them first and the other parts as these run out.  What bounds it is how many
+// lines are read, and how many work-groups that are free together take the same instance and find
+// its electrons gone.  With all instances looked at by every work-group, and the work alone as the key,
+// 4000 instances of 64 electrons x 300 collisions took 103 ms (FP32) and now take 4.4, 1000 x 10
+// 147 and 2.5, uneven ones 133 and 34; all instances and the key per work-group 56, 132 and 94,
+// parts of 256 instances 4.8, 2.6 and 33; 256 x 1000 x 2000 24.5 and 23.5.
+constexpr int kHelpAmong = 64;
+// State of a work-group's walk over the instances, in LDS: what the plan says is kept here too,
+// as scalar registers would hold it (or spill it) through all of the trials.
+struct GroupWalk {
+  unsigned long long* taken;
+  const float* weight;
+  const uint32_t* count;
+  unsigned long long best;
+  int n_inst;
+  int empty;                    // parts of the instances found without electrons to take
+};
+__device__ __forceinline__ unsigned long long* taken_of(const GroupWalk& walk, int i) {
+  return walk.taken + static_cast<int64_t>(i) * kClaimStride;
+}
+__device__ __forceinline__ int first_instance(const ClaimPlan& plan, GroupWalk& walk) {
+  const int inst = plan.first != nullptr ? __builtin_amdgcn_readfirstlane(plan.first[blockIdx.x]) : 0;
+  if (threadIdx.x == 0) {
+    walk.taken = plan.taken;
+    walk.weight = plan.weight;
+    walk.count = plan.count;
+    walk.n_inst = plan.n_inst;
+    walk.empty = 0;
+    if (plan.n_inst > 1) atomicAdd(plan.taken + static_cast<int64_t>(inst) * kClaimStride + 1, 1ull);
+  }
+  return inst;
+}
+__device__ __forceinline__ int next_instance(GroupWalk& walk) {
   __syncthreads();
-  if (threadIdx.x == 0) *s_best = 0ull;
-  __syncthreads();
-  for (int i = threadIdx.x; i < plan.n_inst; i += blockDim.x) {
-    const int64_t left = descs[i].n_electrons -
-        static_cast<int64_t>(__hip_atomic_load(&plan.taken[static_cast<int64_t>(i) * kClaimStride], __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT));
-    if (left > 0) {
-      const uint32_t key = __float_as_uint(static_cast<float>(left) * plan.weight[i]);    // positive: ordered as bits
-      atomicMax(s_best, (static_cast<unsigned long long>(key) << 32) | static_cast<uint32_t>(0x7fffffff - i));
+  const int n_inst = __builtin_amdgcn_readfirstlane(walk.n_inst);
+  if (n_inst == 1) return -1;
+  const int parts = (n_inst + kHelpAmong - 1) / kHelpAmong;
+  for (int empty = __builtin_amdgcn_readfirstlane(walk.empty); empty < parts; ++empty) {
+    const int part = static_cast<int>((blockIdx.x + static_cast<uint32_t>(empty)) % static_cast<uint32_t>(parts));
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      walk.best = 0ull;
+      walk.empty = empty;
+    }
+    __syncthreads();
+    for (int i = part + static_cast<int>(threadIdx.x) * parts; i < n_inst; i += static_cast<int>(blockDim.x) * parts) {
+      unsigned long long* c = taken_of(walk, i);
+      const unsigned long long taken = __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned long long on = __hip_atomic_load(c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int64_t left = static_cast<int64_t>(walk.count[i]) - static_cast<int64_t>(taken);
+      if (left > 0) {
+        const float work = static_cast<float>(left) * walk.weight[i] / static_cast<float>(on + 1);
+        const uint32_t key = __float_as_uint(work);    // positive: ordered as bits
+        atomicMax(&walk.best, (static_cast<unsigned long long>(key) << 32) | static_cast<uint32_t>(0x7fffffff - i));
+      }
+    }
+    __syncthreads();
+    const uint64_t best = static_cast<uint64_t>(wave_uniform(static_cast<int64_t>(walk.best)));
+    if (best != 0ull) {
+      const int inst = 0x7fffffff - static_cast<int>(static_cast<uint32_t>(best));
+      if (threadIdx.x == 0) atomicAdd(taken_of(walk, inst) + 1, 1ull);
+      return inst;
     }
   }
-  __syncthreads();
-  const unsigned long long best = *s_best;
-  return best == 0ull ? -1 : __builtin_amdgcn_readfirstlane(0x7fffffff - static_cast<int>(static_cast<uint32_t>(best)));
+  return -1;
 }
 
 // Waves per SIMD the registers of the dummy kernel have to allow (asked for where the compiler
@@ -1943,9 +1991,8 @@ __global__ void __launch_bounds__(512, (dummy_waves<R, HB, TR, EXT>())) k_swarm_
   PT* s_nu = reinterpret_cast<PT*>(smem);
   __shared__ __align__(16) double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
-  __shared__ unsigned long long s_best;
-  int inst = plan.first != nullptr ? __builtin_amdgcn_readfirstlane(plan.first[blockIdx.x]) : 0;
-  for (; inst >= 0; inst = next_instance(descs, plan, &s_best)) {
+  __shared__ GroupWalk s_walk;
+  for (int inst = first_instance(plan, s_walk); inst >= 0; inst = next_instance(s_walk)) {
     const InstanceDesc& d = descs[inst];
     stage_instance<R>(d, smem, s_ch, s_logtab, cum_off);
     __syncthreads();
@@ -1956,7 +2003,7 @@ __global__ void __launch_bounds__(512, (dummy_waves<R, HB, TR, EXT>())) k_swarm_
       C.cum = reinterpret_cast<const PT*>(smem + cum_off);
       C.cum_lds = true;
     }
-    unsigned long long* taken = plan.taken + static_cast<int64_t>(inst) * kClaimStride;
+    unsigned long long* taken = taken_of(s_walk, inst);
     const uint32_t count = static_cast<uint32_t>(d.n_electrons);
     WaveClaim claims;
     Lane<R> L;
@@ -2117,20 +2164,23 @@ __device__ __forceinline__ void team_trials(Lane<R>& L, const Consts<R>& C,
     team_blocks<R, HB, EXT>(L, C, s_nu, t);
 }
 
+// (97 registers without the bound; 96 allow five waves.)
 template <typename R, bool HB, int EXT>
-__global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restrict__ descs, ClaimPlan plan,
+constexpr int team_waves() { return sizeof(R) == 4 && !HB && EXT == 0 ? 5 : 1; }
+
+template <typename R, bool HB, int EXT>
+__global__ void __launch_bounds__(512, (team_waves<R, HB, EXT>())) k_swarm_team(const InstanceDesc* __restrict__ descs, ClaimPlan plan,
                                                     int pend_trig, int ch_off, int cum_off, int g, int per_wave) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
   PT* s_nu = reinterpret_cast<PT*>(smem);
   __shared__ __align__(16) double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
-  __shared__ unsigned long long s_best;
+  __shared__ GroupWalk s_walk;
   const int lane = static_cast<int>(threadIdx.x) & 63;
   const TeamLane team = {g, lane & (g - 1), lane & ~(g - 1)};
   const uint64_t firsts = __ballot(team.sub == 0);
-  int inst = plan.first != nullptr ? __builtin_amdgcn_readfirstlane(plan.first[blockIdx.x]) : 0;
-  for (; inst >= 0; inst = next_instance(descs, plan, &s_best)) {
+  for (int inst = first_instance(plan, s_walk); inst >= 0; inst = next_instance(s_walk)) {
     const InstanceDesc& d = descs[inst];
     stage_instance<R>(d, smem, s_ch, s_logtab, cum_off);
     __syncthreads();
@@ -2141,7 +2191,7 @@ __global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restri
       C.cum = reinterpret_cast<const PT*>(smem + cum_off);
       C.cum_lds = true;
     }
-    unsigned long long* taken = plan.taken + static_cast<int64_t>(inst) * kClaimStride;
+    unsigned long long* taken = taken_of(s_walk, inst);
     const uint32_t count = static_cast<uint32_t>(d.n_electrons);
     WaveClaim claims;
     Lane<R> L;
@@ -2339,7 +2389,7 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
   PT* s_nu = reinterpret_cast<PT*>(smem);
   __shared__ __align__(16) double s_logtab[sizeof(R) == 8 ? kUnitLogStride * kUnitLogEntries : 1];
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
-  __shared__ unsigned long long s_best;
+  __shared__ GroupWalk s_walk;
   __shared__ int s_ncand[2];   // pool slots asked for, by round parity
   __shared__ int s_live[3];    // some electron of the item is not done, by round mod 3
   const int wave = static_cast<int>(threadIdx.x) >> 6;
@@ -2352,8 +2402,7 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
   P.r = reinterpret_cast<R*>(P.d + kPoolD * P.cap);
   P.u = reinterpret_cast<uint32_t*>(P.r + kPoolR * P.cap);
   const uint64_t lane_lt = (1ull << lane) - 1ull;
-  int inst = plan.first != nullptr ? __builtin_amdgcn_readfirstlane(plan.first[blockIdx.x]) : 0;
-  for (; inst >= 0; inst = next_instance(descs, plan, &s_best)) {
+  for (int inst = first_instance(plan, s_walk); inst >= 0; inst = next_instance(s_walk)) {
     const InstanceDesc& d = descs[inst];
     stage_instance<R>(d, smem, s_ch, s_logtab, cum_off);
     if (threadIdx.x == 0) {
@@ -2393,7 +2442,7 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
       }
     } else {
       // ---- trial waves ----
-      unsigned long long* taken = plan.taken + static_cast<int64_t>(inst) * kClaimStride;
+      unsigned long long* taken = taken_of(s_walk, inst);
       const uint32_t count = static_cast<uint32_t>(d.n_electrons);
       WaveClaim claims;
       Lane<R> L;

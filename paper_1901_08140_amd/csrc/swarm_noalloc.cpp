@@ -141,7 +141,7 @@ swarm_status swarm_run_noalloc(swarm_t h, int64_t n_electrons, int64_t n_collisi
     return hip_fail(e, "descriptor");
   if ((e = hipEventRecord(h->ev[0], s)) != hipSuccess) return hip_fail(e, "event");
   const int grid = static_cast<int>(std::min<int64_t>((n_electrons + per_group - 1) / per_group, slots));
-  const ClaimPlan plan = {reinterpret_cast<unsigned long long*>(&d.ctr->gen_next), nullptr, nullptr, 1, wave_chunk(o)};
+  const ClaimPlan plan = {reinterpret_cast<unsigned long long*>(&d.ctr->gen_next), nullptr, nullptr, nullptr, 1, wave_chunk(o)};
   if ((e = launch_swarm_dummy(h->d_desc, plan, d.precision, h->has_b, false, ext, o.service_waves, o.block_size, grid,
                               o.pending_trigger, ll.bytes, ll.ch_off, ll.pool_off, ll.cum_off, s, team)) != hipSuccess)
     return hip_fail(e, "swarm kernel launch");
