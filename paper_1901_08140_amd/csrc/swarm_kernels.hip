@@ -2003,7 +2003,7 @@ __global__ void __launch_bounds__(512, (dummy_waves<R, HB, TR, EXT>())) k_swarm_
       C.cum = reinterpret_cast<const PT*>(smem + cum_off);
       C.cum_lds = true;
     }
-    unsigned long long* taken = taken_of(s_walk, inst);
+    unsigned long long* taken = reinterpret_cast<unsigned long long*>(wave_uniform(reinterpret_cast<int64_t>(taken_of(s_walk, inst))));
     const uint32_t count = static_cast<uint32_t>(d.n_electrons);
     WaveClaim claims;
     Lane<R> L;
@@ -2164,12 +2164,8 @@ __device__ __forceinline__ void team_trials(Lane<R>& L, const Consts<R>& C,
     team_blocks<R, HB, EXT>(L, C, s_nu, t);
 }
 
-// (97 registers without the bound; 96 allow five waves.)
 template <typename R, bool HB, int EXT>
-constexpr int team_waves() { return sizeof(R) == 4 && !HB && EXT == 0 ? 5 : 1; }
-
-template <typename R, bool HB, int EXT>
-__global__ void __launch_bounds__(512, (team_waves<R, HB, EXT>())) k_swarm_team(const InstanceDesc* __restrict__ descs, ClaimPlan plan,
+__global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restrict__ descs, ClaimPlan plan,
                                                     int pend_trig, int ch_off, int cum_off, int g, int per_wave) {
   using PT = typename Pair<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -2191,7 +2187,7 @@ __global__ void __launch_bounds__(512, (team_waves<R, HB, EXT>())) k_swarm_team(
       C.cum = reinterpret_cast<const PT*>(smem + cum_off);
       C.cum_lds = true;
     }
-    unsigned long long* taken = taken_of(s_walk, inst);
+    unsigned long long* taken = reinterpret_cast<unsigned long long*>(wave_uniform(reinterpret_cast<int64_t>(taken_of(s_walk, inst))));
     const uint32_t count = static_cast<uint32_t>(d.n_electrons);
     WaveClaim claims;
     Lane<R> L;
@@ -2442,7 +2438,7 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
       }
     } else {
       // ---- trial waves ----
-      unsigned long long* taken = taken_of(s_walk, inst);
+      unsigned long long* taken = reinterpret_cast<unsigned long long*>(wave_uniform(reinterpret_cast<int64_t>(taken_of(s_walk, inst))));
       const uint32_t count = static_cast<uint32_t>(d.n_electrons);
       WaveClaim claims;
       Lane<R> L;
