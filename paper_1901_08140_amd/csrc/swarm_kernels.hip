@@ -491,16 +491,25 @@ __global__ void k_build_constants(InstanceDesc* desc) {
     // The energies spread around the balance node, most of them to lower rates: over gases and
     // fields the trials per real collision beyond the first are about 1.5 times those at the
     // node (argon 100 Td: 2.3 counted, 1.4 at the node; Ar:CO2 31 Td: 3.2 and 1.8; 93:7 at
-    // 2.4 Td: 22.7 and 21).  The adaptive strategies make about 2, and with the
-    // returns to the last collision after fails their runs behave like 4.
+    // 2.4 Td: 22.7 and 21).  The adaptive strategies count 2.1 to 2.6 (binned 2.1 to 5.9), but one
+    // of their trials takes longer, and where the constant frequency would make many, one lane
+    // takes 3.4 to 3.9 us per collision (FP32, argon 1 to 100 Td), for which team_shape's model
+    // needs 8.  With 4 its choice is within 14% of the best one up to 20,000 electrons, 27% from
+    // there to 200,000 (binned 26 and 47%).
     d.trials = 1.0 + 1.5 * (nup / F[min(d.balance_node, static_cast<uint32_t>(d.G - 1))] - 1.0);
-    if (d.trial_strategy != SWARM_TRIAL_CONSTANT) d.trials = fmin(d.trials, 4.0);
+    const bool adaptive = d.trial_strategy != SWARM_TRIAL_CONSTANT;
+    if (adaptive) d.trials = fmin(d.trials, 4.0);
     // The more trials a collision takes, the longer a wave waits for its next candidates and the
     // sooner it should serve those it has.  Argon, 16 x 1e5 electrons, ms with 24, 28, 32, 40 and
     // 48 waiting lanes: 1 Td (trials 8) FP32 271, 270, 282, 289, 325 and FP64 347, 352, 356, 391,
     // 456; 3 Td (4.3) FP32 163, 161, 158, 159, 169 and FP64 198, 195, 194, 200, 219; 100 Td (3.1)
     // FP32 83, 82, 79, 76, 78 and FP64 93, 91, 88, 84, 86; 1000 Td (1.7) the same for all.
-    d.trigger = d.trials >= 6.0 ? 26 : d.trials >= 3.8 ? 32 : 40;
+    // The adaptive strategies have a dearer collision (a new nu', and the test for fails) and few
+    // trials at any field.  16 x 50,000 x 1000, with 24, 32, 40, 44, 48 and 56: variable 3 Td FP32
+    // 12.7, 12.2, 12.2, 11.9, 11.7, 11.9, 100 Td FP64 31.8, 31.7, 29.8, 29.5, 29.7, 31.0, binned 3 Td
+    // FP32 21.9, 20.9, 19.6, 18.9, 18.8, 18.4, FP64 46.9, 45.3, 41.7, 40.7, 41.4, 44.1, with moving
+    // targets FP64 at 3 Td 49.2, 50.0, 48.8, 47.7, 46.9, 45.0.
+    d.trigger = adaptive ? 48 : d.trials >= 6.0 ? 26 : d.trials >= 3.8 ? 32 : 40;
     d.inv_majorant = 1.0 / nup;
     d.majorant_f = static_cast<float>(nup);
     d.cT_f = static_cast<float>(kLn2 / nup);
