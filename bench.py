@@ -534,7 +534,6 @@ def main():
     opts = {"use_graph": 1}
     if args.autotune:
         # probe budgets of a fifth of the run's: short probes misjudge the end of the launch
-        # (the tail of the last work items), which the work-item size is about
         best = sw.swarm_autotune(handles, jobs, max(300, args.collisions // 5))
         opts.update(best)
         opts["use_graph"] = 1

@@ -355,7 +355,9 @@ typedef struct {
   int32_t use_graph;       /* capture the launch in a hipGraph and replay it */
   int32_t service_waves;   /* 0: every wave serves its own candidates; n >= 1: pooled schedule,
                               n waves of each work-group serve the candidates of the others at
-                              full width (n < block_size/64; traced runs use the per-wave one) */
+                              full width (n < block_size/64; traced runs use the per-wave one);
+                              -1: the library's own shape, as with zeros in this and the fields
+                              block_size, chunk and pending_trigger, which are not used */
   int32_t table_layout;    /* LDS tables of a work-group: 0 the total-rate pairs and channel
                               descriptors (running sums read through L2); 1 also the running
                               sums of every channel, when they fit the work-group's LDS
@@ -396,9 +398,10 @@ void swarm_batch_destroy(swarm_batch_t b);
 swarm_status swarm_batch_run(swarm_t* handles, const swarm_job* jobs, int32_t n,
                              const swarm_launch_opts* opts);
 
-/* Autotuner: times the result-invariant launch options (block size, pending trigger, electrons
- * per claim, LDS table layout) on a shortened copy of the batch
- * (same instances, budgets cut to probe_collisions) and writes the fastest to *best. */
+/* Autotuner: times the result-invariant launch options (the library's own shape, block size,
+ * pending trigger, LDS table layout) on a shortened copy of the batch
+ * (same instances, budgets cut to probe_collisions) and writes the fastest to *best.  Where the
+ * library's own shape is, best->service_waves is -1. */
 swarm_status swarm_autotune(swarm_t* handles, const swarm_job* jobs, int32_t n,
                             int64_t probe_collisions, swarm_launch_opts* best);
 

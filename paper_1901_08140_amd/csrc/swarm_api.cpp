@@ -417,15 +417,16 @@ int default_block() { return 256; }
 
 swarm_launch_opts resolve_opts(const swarm_launch_opts* o) {
   swarm_launch_opts r{};
-  r.block_size = (o && o->block_size) ? o->block_size : default_block();
+  const bool own = o && o->service_waves >= 0;      // (-1: the shape is left to the library)
+  r.block_size = (own && o->block_size) ? o->block_size : default_block();
   // electrons the lanes of a work-group take at a time, one each: any number from a half to four
   // gave the same time (argon sweep 311 ms x 8000 collisions, FP64 252 to 255 ms x 2000)
-  r.chunk = (o && o->chunk) ? o->chunk : r.block_size;
+  r.chunk = (own && o->chunk) ? o->chunk : r.block_size;
   r.use_graph = o ? o->use_graph : 0;
   r.block_size = std::max(64, std::min(1024, (r.block_size / 64) * 64));
   r.chunk = std::max(r.block_size, (r.chunk / r.block_size) * r.block_size);
   // (0 stays: every instance's own number, from the trials its collisions take)
-  r.pending_trigger = o && o->pending_trigger ? std::max(1, std::min(64, o->pending_trigger)) : 0;
+  r.pending_trigger = own && o->pending_trigger ? std::max(1, std::min(64, o->pending_trigger)) : 0;
   r.service_waves = o ? std::max(0, std::min(r.block_size / 64 - 1, o->service_waves)) : 0;
   r.table_layout = (o && o->table_layout == 1) ? 1 : 0;
   r.park_lanes = (o && o->park_lanes) ? std::max(-1, std::min(64, o->park_lanes)) : kParkLanes;
@@ -433,7 +434,8 @@ swarm_launch_opts resolve_opts(const swarm_launch_opts* o) {
 }
 
 bool free_shape(const swarm_launch_opts* o) {
-  return !o || (o->block_size == 0 && o->chunk == 0 && o->pending_trigger == 0 && o->service_waves == 0);
+  return !o || o->service_waves < 0 ||
+         (o->block_size == 0 && o->chunk == 0 && o->pending_trigger == 0 && o->service_waves == 0);
 }
 
 // A team of g lanes makes about one step per collision once 2 g exceeds the trials t that a

@@ -265,11 +265,12 @@ swarm_status swarm_batch_run(swarm_t* handles, const swarm_job* jobs, int32_t n,
   return st;
 }
 
-// Coordinate search over the result-invariant launch options on a probe copy of the batch
-// (same instances and electron counts, budgets cut to probe_collisions): block size, then
-// the pending-lane trigger, then the work-item size, then the LDS table layout.  Each
-// candidate takes the faster of two launches (one launch varies by a few percent), after
-// one untimed launch of the default shape.
+// Search over the result-invariant launch options on a probe copy of the batch (same instances and
+// electron counts, budgets cut to probe_collisions): the library's own shape (teams of lanes for few
+// electrons, every instance's own trigger); one lane per electron with each block size, then with
+// each trigger; then the LDS table layout of the faster of the two.  (The electrons per claim change
+// nothing that can be measured.)  Each candidate takes the faster of two launches (one launch
+// varies by a few percent), after an untimed launch of the first.
 swarm_status swarm_autotune(swarm_t* handles, const swarm_job* jobs, int32_t n, int64_t probe_collisions,
                             swarm_launch_opts* best) {
   if (!best || !handles || !jobs || n <= 0) return fail(SWARM_ERR_INVALID_ARG, "NULL argument");
@@ -290,41 +291,38 @@ swarm_status swarm_autotune(swarm_t* handles, const swarm_job* jobs, int32_t n, 
     swarm_batch_destroy(b);
     return st;
   };
-  swarm_launch_opts cur = resolve_opts(nullptr);
-  cur.use_graph = 0;
-  cur.pending_trigger = 32;   // probed below; the options returned hold one number for all
-  double t = 0.0;
-  swarm_status st = time_it(cur, &t);   // warm-up
+  const swarm_launch_opts base = resolve_opts(nullptr);
+  swarm_launch_opts free = base;
+  free.service_waves = -1;
+  free.pending_trigger = 32;      // (not used)
+  double t_free = 0.0, t = 0.0;
+  swarm_status st = time_it(free, &t_free);   // warm-up
+  if (st == SWARM_OK) st = time_it(free, &t_free);
   if (st != SWARM_OK) return st;
-  double best_t = 1e300;
-  const int per_lane = cur.chunk / cur.block_size;   // the precision's default
+  swarm_launch_opts one = base;
+  double t_one = 1e300;
   for (int bs : {128, 256, 512}) {
-    swarm_launch_opts o = cur;
+    swarm_launch_opts o = base;
     o.block_size = bs;
-    o.chunk = bs * per_lane;
+    o.chunk = bs;
+    o.pending_trigger = 32;
     if ((st = time_it(o, &t)) != SWARM_OK) return st;
-    if (t < best_t) { best_t = t; cur = o; }
+    if (t < t_one) { t_one = t; one = o; }
   }
-  const swarm_launch_opts base1 = cur;
-  for (int trig : {16, 24, 32, 40, 48}) {
-    swarm_launch_opts o = base1;
+  const swarm_launch_opts best_block = one;
+  for (int trig : {16, 24, 40, 48}) {
+    swarm_launch_opts o = best_block;
     o.pending_trigger = trig;
     if ((st = time_it(o, &t)) != SWARM_OK) return st;
-    if (t < best_t) { best_t = t; cur = o; }
+    if (t < t_one) { t_one = t; one = o; }
   }
-  const swarm_launch_opts base2 = cur;
-  for (int mult : {2, 3, 4, 8}) {
-    swarm_launch_opts o = base2;
-    o.chunk = base2.block_size * mult;
-    if ((st = time_it(o, &t)) != SWARM_OK) return st;
-    if (t < best_t) { best_t = t; cur = o; }
-  }
+  swarm_launch_opts cur = t_one < t_free ? one : free;
   // LDS table layout: running sums in LDS too (taken only where they fit; see lds_layout)
   {
     swarm_launch_opts o = cur;
     o.table_layout = 1;
     if ((st = time_it(o, &t)) != SWARM_OK) return st;
-    if (t < best_t) { best_t = t; cur = o; }
+    if (t < std::min(t_one, t_free)) cur = o;
   }
   *best = cur;
   return SWARM_OK;
