@@ -320,7 +320,7 @@ swarm_status swarm_last_team(swarm_t h, int32_t* lanes);
  * swarm_run with no allocation.  The caller passes `records`, device memory for n_electrons
  * swarm_record entries, which receive the records of ids 0..n-1 in id order (as swarm_run
  * keeps them).  The run's scratch (tally tiles, partial sums and
- * output) is a library array of 1.4 MB in device memory, one per GPU, held until the
+ * output) is a library array of 1.0 MB in device memory, one per GPU, held until the
  * process ends; n_electrons is limited to 4194304 (2^22) and larger runs are refused with
  * SWARM_ERR_INVALID_ARG, as are REAL mode and tracing.  Every call on a GPU shares that
  * GPU's array and leaves its contents behind (each call rebuilds what it reads); calls that

@@ -884,9 +884,13 @@ swarm_status run_start(swarm_t h, int64_t n_electrons, int64_t n_collisions, uin
     // 1004 -> 966 ms; waves of at most 16 running lanes parking after half a device of
     // secondaries: 379 and 988 ms; 48 lanes after a sixteenth: 384 and 960 ms).
     //
-    // No more than four waves per SIMD: the collisions of a magnetised mixture wait on L2, and the
+    // No more than four waves per SIMD.  The collisions of a magnetised mixture wait on L2, and the
     // channel rows of more waves crowd it (100,000 primaries 73.3 ms with five, 70.4 with four, 72.0
-    // with three; 1e6 primaries x 1000 76.6 and 72.4 with five and four).
+    // with three; 1e6 primaries x 1000 76.6 and 72.4 with five and four).  Argon's five channels
+    // do not, but its generations of some rounds end earlier too on fewer lanes (FP32, five and four:
+    // 300,000 x 1000 at 100 Td 28.0 and 25.9, x 1500 at 30 Td 15.5 and 14.6, 1e6 x 100 at 100 Td 6.8
+    // and 6.3); where many primaries ionise little it would gain from five (1e6 x 300 at 30 Td 8.9
+    // and 9.7, 1e6 x 1000 at 10 Td 24.5 and 25.7).
     const int groups_per_cu = std::max(1, std::min(per_cu, 16 * 64 / o.block_size));
     const int64_t lanes = static_cast<int64_t>(dev.n_cu) * groups_per_cu * o.block_size;
     const int park_lanes = std::max(0, o.park_lanes);   // -1: never

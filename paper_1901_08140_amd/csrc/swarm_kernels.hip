@@ -1439,19 +1439,19 @@ __device__ __forceinline__ uint32_t team_bits(uint64_t mask, const TeamLane& t) 
   return static_cast<uint32_t>(mask >> t.base) & (0xffffffffu >> (32 - t.g));
 }
 
-// Channel of a candidate by a whole team: the running sums of the row are compared by its
+// Channel of a candidate by a whole team, for rows that one lane would bisect (more than
+// kScanChannels): the running sums of the row are compared by the team's
 // lanes, up to four each, in one memory round trip (bisection takes one per halving, and a
-// lone wave waits for each).  The answer is the one-lane kernel's to the bit: the first c
-// with x < C_c for few channels, else what bisection gives, which differs only where the
-// rounding of the interpolated sums makes them decrease; the few comparisons are then
-// bisected in registers.
+// lone wave waits for each).  The answer is the one-lane kernel's to the bit: the first c with
+// x < C_c, or where the rounding of the interpolated sums makes them decrease what bisection
+// gives; the few comparisons are then bisected in registers.
 template <typename R>
 __device__ __forceinline__ int team_channel(const Consts<R>& C, const typename Pair<R>::T* row, R x, R w,
                                             const TeamLane& t) {
   using PT = typename Pair<R>::T;
   int lo = 0, hi = C.nc - 1;
   const int at_once = min(4 * t.g, 64);
-  while (C.nc > kScanChannels && hi - lo > at_once) {
+  while (hi - lo > at_once) {
     const int mid = (lo + hi) >> 1;
     if (x < lerp_pair(row[mid], w)) hi = mid; else lo = mid + 1;
   }
@@ -1467,7 +1467,7 @@ __device__ __forceinline__ int team_channel(const Consts<R>& C, const typename P
     if (i * t.g < 64) below |= b << (i * t.g);
   }
   const int z = below != 0 ? __ffsll(static_cast<long long>(below)) - 1 : n;
-  if (C.nc <= kScanChannels || z == n || (below >> z) == (~0ull >> (64 - (n - z)))) return lo + z;
+  if (z == n || (below >> z) == (~0ull >> (64 - (n - z)))) return lo + z;
   int a = 0, b = n;
   while (a < b) {
     const int mid = (a + b) >> 1;
@@ -2396,7 +2396,7 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
   ChannelDev* s_ch = reinterpret_cast<ChannelDev*>(smem + ch_off);
   __shared__ GroupWalk s_walk;
   __shared__ int s_ncand[2];   // pool slots asked for, by round parity
-  __shared__ int s_live[3];    // some electron of the item is not done, by round mod 3
+  __shared__ int s_live[3];    // some electron of the instance is not done, by round mod 3
   const int wave = static_cast<int>(threadIdx.x) >> 6;
   const int lane = static_cast<int>(threadIdx.x) & 63;
   const int n_trial = static_cast<int>(blockDim.x >> 6) - n_service;
