@@ -2012,7 +2012,11 @@ __global__ void __launch_bounds__(512, (dummy_waves<R, HB, TR, EXT>())) k_swarm_
       C.cum = reinterpret_cast<const PT*>(smem + cum_off);
       C.cum_lds = true;
     }
-    unsigned long long* taken = reinterpret_cast<unsigned long long*>(wave_uniform(reinterpret_cast<int64_t>(taken_of(s_walk, inst))));
+    // (FP64 with B is short of scalar registers too: with the address from the kernel's arguments it was
+    // 2% slower, the Maxwell gas 5.86 -> 6.0 ms; the other kernels are up to 4% faster with that.)
+    unsigned long long* taken = plan.taken + static_cast<int64_t>(inst) * kClaimStride;
+    if constexpr (sizeof(R) == 8 && HB)
+      taken = reinterpret_cast<unsigned long long*>(wave_uniform(reinterpret_cast<int64_t>(taken_of(s_walk, inst))));
     const uint32_t count = static_cast<uint32_t>(d.n_electrons);
     WaveClaim claims;
     Lane<R> L;
@@ -2196,7 +2200,7 @@ __global__ void __launch_bounds__(512) k_swarm_team(const InstanceDesc* __restri
       C.cum = reinterpret_cast<const PT*>(smem + cum_off);
       C.cum_lds = true;
     }
-    unsigned long long* taken = reinterpret_cast<unsigned long long*>(wave_uniform(reinterpret_cast<int64_t>(taken_of(s_walk, inst))));
+    unsigned long long* taken = plan.taken + static_cast<int64_t>(inst) * kClaimStride;
     const uint32_t count = static_cast<uint32_t>(d.n_electrons);
     WaveClaim claims;
     Lane<R> L;
@@ -2447,7 +2451,7 @@ __global__ void __launch_bounds__(512) k_swarm_pooled(const InstanceDesc* __rest
       }
     } else {
       // ---- trial waves ----
-      unsigned long long* taken = reinterpret_cast<unsigned long long*>(wave_uniform(reinterpret_cast<int64_t>(taken_of(s_walk, inst))));
+      unsigned long long* taken = plan.taken + static_cast<int64_t>(inst) * kClaimStride;
       const uint32_t count = static_cast<uint32_t>(d.n_electrons);
       WaveClaim claims;
       Lane<R> L;
