@@ -1824,7 +1824,7 @@ __device__ __forceinline__ void stage_cum(const InstanceDesc& d, unsigned char* 
 // wave (or one that never was full) waits until its last running lane holds a candidate, and
 // the launch waits for it.  One FP64 argon swarm of 100,000 electrons x 2000 collisions went
 // from 98.7 to 64.5 ms at 1 Td and from 21.4 to 20.3 ms at 10 Td, FP32 50.4 to 28.7 and 9.4 to
-// 8.5 ms, the batched argon sweep (32 x 1e5 x 2e4, FP32) from 782 to 751 ms.  (The launches of
+// 8.5 ms.  (The launches of
 // real-secondaries runs keep the fixed number: their draining waves park, and serving them
 // in smaller groups took 78.5 against 75.8 ms for 1e5 primaries of the magnetised mixture.)
 __device__ __forceinline__ int wave_trigger(bool drawing, int pend_trig) {
@@ -1987,7 +1987,7 @@ constexpr int dummy_waves() {
 // with a wait for the slowest lane at each item's end, was slower the more the electrons' times
 // differ (ms, items | now): 20 argon fields x 60,000 x 5000 FP32 117 | 97 (first launch, nothing
 // measured yet, 164 | 91), 10 x 60,000 x 1000 FP64 69 | 43 (126 | 41), the argon sweep 32 x 1e5
-// x 2e4 FP32 743 | 721; 16 adaptive fields x 50,000, all alike, 50.6 | 51.8.
+// x 2e4 FP32 743 | 721; 16 adaptive fields x 50,000, all alike, 50.6 | 50.6.
 // Lanes that reach a real-collision candidate wait; the wave serves all waiting lanes together
 // once wave_trigger() of them wait (or no lane can make progress otherwise), which keeps the
 // costly collision code from running for one lane at a time.
